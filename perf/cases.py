@@ -330,3 +330,91 @@ def tolerance(case):
     if path == "cube" and out == "bf16":        # bf16 partial products, summed and rounded again: 2.4e-3
         return {"rel": 1e-2, "max": 6e-2}
     return {"rel": 6e-3, "max": 1.6e-2}         # one bf16 rounding: 1.7e-3
+
+
+# ---- the same results in 64 bits ----------------------------------------------------------------------
+
+def _f64(t, scale=1.0):
+    return t.float().double() * scale
+
+
+def _by_direction(t, q, axis):
+    """Cube buffer as [i, a, b, ...]: a along the input direction, b along the output direction."""
+    t = t.reshape(q, q, q, *t.shape[1:])
+    return t if axis == c3.AXIS_Y else t.transpose(1, 2)
+
+
+# order of (i, a, b, rows of a shard, columns of a shard) in the full matrix: (row indices), (column indices)
+_ORDER = {"x": ((0, 1, 3), (2, 4)), "w": ((2, 3), (1, 0, 4)), "y": ((0, 2, 3), (1, 4))}
+
+
+def _whole(which, t, q, axis=c3.AXIS_Y):
+    """Full matrix of a cube of shards."""
+    rows, cols = _ORDER[which]
+    t = _by_direction(t, q, axis).permute(*rows, *cols)
+    return t.reshape(t.shape[:len(rows)].numel(), -1)
+
+
+def _spread(which, full, q, axis=c3.AXIS_Y):
+    """Cube of shards of a full matrix."""
+    rows, cols = _ORDER[which]
+    cut = lambda n, order: [q] * (len(order) - 1) + [n // q ** (len(order) - 1)]
+    order = rows + cols
+    t = full.reshape(*cut(full.shape[0], rows), *cut(full.shape[1], cols)).permute(*[order.index(d) for d in range(5)])
+    t = t if axis == c3.AXIS_Y else t.transpose(1, 2)
+    return t.reshape(q ** 3, *t.shape[3:])
+
+
+def _whole_bias(t, q):
+    return t.reshape(q, q, q, -1).diagonal(dim1=1, dim2=2).permute(2, 0, 1).reshape(-1)
+
+
+def _spread_bias(full, q):
+    t = full.new_zeros(q, q, q, full.numel() // q ** 2)
+    for a in range(q):
+        t[:, a, a] = full.reshape(q, q, -1)[a]
+    return t.reshape(q ** 3, -1)
+
+
+def exact(case, seed):
+    s, q, path = prepare(case, seed), case["q"], case["path"]
+    if path == "storage":
+        return (_spread("x", _f64(s["X"]), q), _spread("w", _f64(s["W"]), q),
+                _f64(_whole("y", s["y"], q)), _f64(_whole("w", s["dw"], q)))
+    if path.startswith("mlp"):
+        return _exact_mlp(s, q, path == "mlp_train")
+    if path == "forms":
+        sx, sw, sg = s["scales"]
+        x, w, g = _whole("x", s["a"], q), _whole("w", s["b"], q), _whole("y", s["g"], q)
+    else:
+        sx, sw, sg = s["d"].scale_x, s["d"].scale_w, s["d"].scale_dy
+        x, w, g = s["X"], s["W"], s["G"]
+        if path == "cube":
+            x, w, g = _whole("x", x, q), _whole("w", w, q), _whole("y", g, q)
+    x, w, g = _f64(x, sx), _f64(w, sw), _f64(g, sg)
+    y, dx, dw = x @ w, g @ w.t(), x.t() @ g
+    if path == "rank":
+        return y, dx, dw
+    if path == "forms":
+        return _spread("y", y, q), _spread("x", dx, q), _spread("w", dw, q)
+    y += _whole_bias(_f64(s["bias"]), q)
+    return _spread("y", y, q), _spread("x", dx, q), _spread("w", dw, q), _spread_bias(g.sum(0), q)
+
+
+def _exact_mlp(s, q, train):
+    # the hidden activations are the first linear's output (axis y) and the second one's input (axis z)
+    z_ax = c3.AXIS_Z
+    x, w1, w2 = (_f64(t) for t in (_whole("x", s["X"], q), _whole("w", s["W1"], q), _whole("w", s["W2"], q, z_ax)))
+    z = x @ w1 + _whole_bias(_f64(s["b1"]), q)
+    gelu = s["kind"] == c3.ACT_GELU
+    cdf = 0.5 * torch.erfc(z * -0.5 ** 0.5) if gelu else (z > 0).double()
+    h = z * cdf
+    y = h @ w2 + _whole_bias(_f64(s["b2"]), q)
+    out = _spread("y", y, q, z_ax)
+    if not train:
+        return out
+    g = _f64(_whole("y", s["G"], q, z_ax))
+    slope = cdf + z * torch.exp(-0.5 * z * z) * (2 * torch.pi) ** -0.5 if gelu else cdf
+    dz = (g @ w2.t()) * slope
+    return (out, _spread("x", dz @ w1.t(), q), _spread("w", x.t() @ dz, q), _spread("w", h.t() @ g, q, z_ax),
+            _spread_bias(dz.sum(0), q), _spread_bias(g.sum(0), q))
