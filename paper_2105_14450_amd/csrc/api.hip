@@ -104,6 +104,14 @@ size_t workspace_for(const GemmArgs &a)
     return gemm_fast_workspace(a);
 }
 
+// The first kernel family that takes the product: tile-aligned sizes, then any size, then operands of 4 GB and more.
+int run_gemm(const GemmArgs &a)
+{
+    int rc = gemm_fast(a);
+    if (rc == CUBE3D_ENOTIMPL) rc = gemm_edge(a);
+    return rc == CUBE3D_ENOTIMPL ? gemm_generic(a) : rc;
+}
+
 int run_product(const cube3d_desc *d, int op, int i, int j, int l, const void *A, const void *B, void *C, void *ws,
                 size_t ws_bytes, void *stream)
 {
@@ -118,9 +126,7 @@ int run_product(const cube3d_desc *d, int op, int i, int j, int l, const void *A
     if (rc != CUBE3D_OK) return rc;
     const size_t need = workspace_for(a);
     if (need > 0 && (!ws || ws_bytes < need)) return CUBE3D_EWORKSPACE;
-    rc = gemm_fast(a);
-    if (rc != CUBE3D_ENOTIMPL) return rc;
-    return gemm_generic(a);
+    return run_gemm(a);
 }
 
 // Where the indices of the full matrices land in the cube buffers of shards (Section 3.1.1):
@@ -190,9 +196,7 @@ int run_cube_product(const cube3d_desc *d, int op, const void *A, const void *B,
     }
     if (mp.bias == nullptr) mp.bias_n = sm.bn;
     a.maps = &mp;
-    rc = gemm_fast(a);
-    if (rc != CUBE3D_ENOTIMPL) return rc;
-    return gemm_generic(a);
+    return run_gemm(a);
 }
 
 // ---- built-in scratch of the entry point that may not allocate --------------------------------------------
@@ -547,9 +551,7 @@ int virtual_cube_matmul(int form, const cube3d_matrix *A, const cube3d_matrix *B
     a.alpha = fp8 ? scale_a * scale_b : 1.f;
     a.stream = static_cast<hipStream_t>(stream);
     a.maps = &mp;
-    rc = gemm_fast(a);
-    if (rc != CUBE3D_ENOTIMPL) return rc;
-    return gemm_generic(a);
+    return run_gemm(a);
 }
 
 size_t cube3d_matmul_workspace_bytes(const cube3d_matmul *mm)
@@ -573,9 +575,7 @@ int cube3d_matmul_blocks(const cube3d_matmul *mm, const void *A_blocks, const vo
     a.stream = static_cast<hipStream_t>(stream);
     const size_t need = workspace_for(a);
     if (need > 0 && (!workspace || workspace_bytes < need)) return CUBE3D_EWORKSPACE;
-    rc = gemm_fast(a);
-    if (rc != CUBE3D_ENOTIMPL) return rc;
-    return gemm_generic(a);
+    return run_gemm(a);
 }
 
 }  // extern "C"

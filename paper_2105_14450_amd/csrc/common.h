@@ -115,6 +115,9 @@ struct GemmArgs {
 // Any shape, any supported dtype; bounds-checked.  Returns a cube3d_status.
 int gemm_generic(const GemmArgs &g);
 
+// Any size and dtype whose operands span less than 4 GB; CUBE3D_ENOTIMPL otherwise.
+int gemm_edge(const GemmArgs &g);
+
 // Tuned bf16 / fp8 path; returns CUBE3D_ENOTIMPL when the shape does not fit its tiles.
 int gemm_fast(const GemmArgs &g);
 size_t gemm_fast_workspace(const GemmArgs &g);

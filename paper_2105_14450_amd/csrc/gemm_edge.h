@@ -1,0 +1,407 @@
+// Product kernel without size classes, for gfx950: any Mo, No and Kc, fp32 / bf16 / fp8-e4m3 operands, plain
+// leading dimensions or a cube of shards read in place.  It takes what the tile-aligned kernel
+// (gemm_mfma_kernel.h) declines: ragged sizes, few rows, fp32.  The local products of Algorithm 1 step 3 and
+// Algorithm 2 lines 1-2.
+//
+// Work split.  A workgroup of four wavefronts (2 x 2) makes a T x T tile (T = 128 or 64), a wavefront a
+// T/2 x T/2 sub-tile in 32x32 MFMA accumulators.  K-tiles are 128 bytes of the contraction index per row.
+// Operands go through registers into LDS: the loads of K-tile t+1 are issued before the MFMAs of K-tile t
+// and written to the other LDS buffer behind them, one barrier per K-tile, so a load has a whole K-tile of
+// MFMAs, times the workgroups that share the CU, to arrive.  Registers rather than direct-to-LDS loads because
+// a piece may be narrower than 16 bytes, may lie in another shard than its neighbour, and has to be zero
+// beyond the last contraction index.
+//
+// Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
+// stored), so only the last, partial K-tile looks at its bounds: it reads element 0 instead and writes zeros.
+// An operand is read in pieces of GB bytes: the widest power of two, up to 16, that divides every distance and
+// extent along the contiguous index, so no piece straddles a row, a shard or the buffer's end.
+//
+// Address arithmetic.  Plain operands are a map with one endless panel.  A lane keeps the walk along the
+// contraction index as (byte offset, position in the shard, shard in the block): a K-tile step is an add, a
+// compare and, rarely, the jump to the next shard or block; nothing is divided inside the loop.
+#pragma once
+#include "common.h"
+
+namespace cube3d {
+namespace edge {
+
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+constexpr int BKB = 128;      // bytes of contraction index per K-tile and row
+
+// Element traits.  A step is what one LDS fragment covers: KSTEP contraction indices, lane half h holding
+// [h * KSTEP / 2, (h + 1) * KSTEP / 2) of them for both kinds of operand.
+//   mn_swz: slot permutation of an MN-major row (spr 16-byte slots) in k-row k, so that the k-rows that one
+//   read covers lie in different banks
+struct Bf16 {
+    static constexpr int ELT = 2, KSTEP = 16;
+    typedef i32x4 Frag;
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
+    // bytes [16 * slot, +16) of a K-major row hold 8 k: slot 2 * step + h is a fragment
+    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
+    {
+        return *reinterpret_cast<const i32x4 *>(row + (((2 * step + h) ^ swz) * 16));
+    }
+    // transposing reads: 16 lanes take 4 k-rows x 16 columns, lane n receives the 4 k of column n
+    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+    {
+        const int g = lane / 16, s = lane % 16;
+        const int k = 8 * (g / 2) + s / 4, byte = (col0 + 16 * (g % 2) + 4 * (s % 4)) * 2;
+        const char *ad = tile + (step * KSTEP + k) * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
+        auto rd = [](const char *a) {
+            return __builtin_bit_cast(i32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) s16x4 *)(__attribute__((address_space(3))) const char *)a));
+        };
+        const i32x2 lo = rd(ad), hi = rd(ad + 4 * RB);
+        return Frag{lo[0], lo[1], hi[0], hi[1]};
+    }
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+};
+
+struct Fp8 {
+    static constexpr int ELT = 1, KSTEP = 16;
+    typedef i32x2 Frag;
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : 2 * ((k >> 2) & 1); }
+    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
+    {
+        return *reinterpret_cast<const i32x2 *>(row + ((step ^ swz) * 16) + 8 * h);
+    }
+    // transposing reads: 16 lanes take 8 k-rows x 16 columns, lane n receives the 8 k of column n
+    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+    {
+        const int g = lane / 16, s = lane % 16;
+        const int k = 8 * (g / 2) + s / 2, byte = col0 + 16 * (g % 2) + 8 * (s % 2);
+        const char *ad = tile + (step * KSTEP + k) * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
+        return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
+            (__attribute__((address_space(3))) i32x2 *)(__attribute__((address_space(3))) const char *)ad);
+    }
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    {
+        return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(__builtin_bit_cast(long, a), __builtin_bit_cast(long, b), c, 0, 0, 0);
+    }
+};
+
+struct F32 {
+    static constexpr int ELT = 4, KSTEP = 8;
+    typedef f32x4 Frag;
+    __device__ static __forceinline__ int mn_swz(int k, int) { return 8 * ((k >> 2) & 1); }
+    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
+    {
+        return *reinterpret_cast<const f32x4 *>(row + (((2 * step + h) ^ swz) * 16));
+    }
+    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+    {
+        const int h = lane / 32, byte = (col0 + lane % 32) * 4;
+        const char *ad = tile + (step * KSTEP + 4 * h) * RB + (((byte / 16) ^ mn_swz(4 * h, RB / 16)) * 16) + byte % 16;
+        Frag f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const float *>(ad + i * RB);
+        return f;
+    }
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
+        return c;
+    }
+};
+
+// Byte distances of an operand's walk along the contraction index.
+struct Walk {
+    unsigned step;     // one K-tile inside a shard
+    unsigned jump2;    // extra when it leaves a shard
+    unsigned jump1;    // extra when it leaves a block as well
+    int P2, shards;    // shard length, shards per block
+};
+
+struct Params {
+    const char *A, *B;
+    char *C;
+    int64_t sA, sB, sC;            // batch strides in bytes
+    int Mo, No, Kc;
+    int tiles_m, tiles_n, group_m;
+    float alpha;
+    int out_f32, out_wide;         // out_wide: 16-byte runs of output columns are aligned and lie in one shard
+    GemmMaps maps;
+    Walk wa, wb;
+};
+
+template <int GB> struct Piece;
+template <> struct Piece<16> { typedef i32x4 Type; };
+template <> struct Piece<8> { typedef i32x2 Type; };
+template <> struct Piece<4> { typedef int Type; };
+template <> struct Piece<2> { typedef unsigned short Type; };
+template <> struct Piece<1> { typedef unsigned char Type; };
+
+// One operand's share of a lane: which pieces it loads, where they go in LDS, and the walk.
+template <typename E, int T, int GB, bool KM> struct Operand {
+    typedef typename Piece<GB>::Type P;
+    static constexpr int SUB = 16 / GB;                 // pieces per 16-byte slot
+    static constexpr int EPS = 16 / E::ELT, EPP = GB / E::ELT;
+    static constexpr int TK = BKB / E::ELT;
+    static constexpr int NP = T * BKB / 16 / 256;       // slots per lane
+    static constexpr int RB = KM ? BKB : T * E::ELT;    // bytes of an LDS row
+    static constexpr int SPR = RB / 16;
+    static constexpr int PASS = 256 / SPR;              // rows between a lane's slots
+    static constexpr int NST = KM ? NP : SUB, NWK = KM ? SUB : NP;
+    static constexpr int BYTES = T * BKB;
+
+    const char *base;
+    unsigned st[NST];          // byte offset of the output index
+    unsigned off[NWK];         // byte offset of the contraction index
+    int pos[NWK], shard[NWK];  // position in the shard, shard in the block
+    int kfirst;                // contraction index of walk 0 inside a K-tile
+    int lds;                   // LDS byte of slot 0
+    P v[NP * SUB];
+
+    __device__ __forceinline__ void init(const char *b, const AxisMap &mn, const AxisMap &km, const Walk &w, int m0, int extent,
+                                         int Kc, int tid)
+    {
+        base = b;
+        const int row = tid / SPR, slot = tid % SPR;
+        // (a lane's rows are PASS apart: a multiple of what the permutations depend on)
+        static_assert(PASS % (KM ? 16 : 8) == 0, "the permutation is the same for a lane's slots");
+        lds = row * RB + ((slot ^ (KM ? (row / 2) % 8 : E::mn_swz(row, SPR))) * 16);
+        kfirst = KM ? slot * EPS : row;
+#pragma unroll
+        for (int i = 0; i < NST; ++i) {
+            const int x = KM ? min(m0 + row + i * PASS, extent - 1) : min(m0 + slot * EPS + i * EPP, extent - EPP);
+            st[i] = (unsigned)(axis_offset_fast(mn, x) * E::ELT);
+        }
+#pragma unroll
+        for (int i = 0; i < NWK; ++i) {
+            const int k = min(kfirst + i * (KM ? EPP : PASS), Kc - 1);   // (beyond Kc the walk is not used)
+            off[i] = (unsigned)(axis_offset_fast(km, k) * E::ELT);
+            const unsigned hi = (unsigned)(((uint64_t)(unsigned)k * km.M1) >> km.N1), r1 = k - hi * km.P1;
+            shard[i] = (int)(((uint64_t)r1 * km.M2) >> km.N2);
+            pos[i] = r1 - shard[i] * w.P2;
+        }
+    }
+
+    // load K-tile number kt, where the walk stands, then move the walk to the next one
+    template <bool TAIL> __device__ __forceinline__ void load(const Walk &w, int k0, int Kc)
+    {
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+            for (int u = 0; u < SUB; ++u) {
+                unsigned o = KM ? st[i] + off[u] : st[u] + off[i];
+                if (TAIL) o = k0 + kfirst + (KM ? u * EPP : i * PASS) < Kc ? o : 0;
+                v[i * SUB + u] = *reinterpret_cast<const P *>(base + o);
+            }
+        if (!TAIL) {
+#pragma unroll
+            for (int i = 0; i < NWK; ++i) {
+                off[i] += w.step;
+                pos[i] += TK;
+                while (pos[i] >= w.P2) {
+                    pos[i] -= w.P2;
+                    off[i] += w.jump2;
+                    if (++shard[i] == w.shards) {
+                        shard[i] = 0;
+                        off[i] += w.jump1;
+                    }
+                }
+            }
+        }
+    }
+
+    template <bool TAIL> __device__ __forceinline__ void store(char *tile, int k0, int Kc)
+    {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            struct alignas(16) Slot { P p[SUB]; } s;
+#pragma unroll
+            for (int u = 0; u < SUB; ++u) {
+                s.p[u] = v[i * SUB + u];
+                if (TAIL && k0 + kfirst + (KM ? u * EPP : i * PASS) >= Kc) s.p[u] = P{};
+            }
+            *reinterpret_cast<i32x4 *>(tile + lds + i * PASS * RB) = __builtin_bit_cast(i32x4, s);
+        }
+    }
+};
+
+template <typename E, int T, int GB, bool AK, bool BK>
+__global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_edge_kernel(const Params p)
+{
+    typedef Operand<E, T, GB, AK> OA;
+    typedef Operand<E, T, GB, BK> OB;
+    typedef typename E::Frag Frag;
+    constexpr int TK = OA::TK, STEPS = TK / E::KSTEP, W = T / 2, NB = W / 32;
+    constexpr int STAGE = OA::BYTES + OB::BYTES;
+    constexpr int STRIP = W * 4 + 16;                   // bytes of a staged output row (fp32, padded)
+    static_assert(4 * 32 * STRIP <= 2 * STAGE, "the output strips reuse the K-tile buffers");
+    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * W, wn = (wave & 1) * W, h = lane >> 5, l32 = lane & 31;
+
+    // Workgroup ids go round robin over the 8 XCDs: hand every XCD one contiguous run of tiles, so that the
+    // panels its workgroups share come through one L2.
+    const int total = gridDim.x, id = blockIdx.x, xcd = id % 8, each = total / 8, more = total % 8;
+    const int item = xcd * each + min(xcd, more) + id / 8;
+    const int tiles = p.tiles_m * p.tiles_n, batch = item / tiles, tile = item - batch * tiles;
+    const int per_group = p.group_m * p.tiles_n, gid = tile / per_group, first_m = gid * p.group_m;
+    const int gsz = min(p.tiles_m - first_m, p.group_m), in_group = tile - gid * per_group;
+    const int m0 = (first_m + in_group % gsz) * T, n0 = (in_group / gsz) * T;
+
+    OA a;
+    OB b;
+    a.init(p.A + batch * p.sA, p.maps.a_mn, p.maps.a_k, p.wa, m0, p.Mo, p.Kc, tid);
+    b.init(p.B + batch * p.sB, p.maps.b_mn, p.maps.b_k, p.wb, n0, p.No, p.Kc, tid);
+
+    f32x16 acc[NB][NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    auto compute = [&](const char *ta) {
+        const char *tb = ta + OA::BYTES;
+        auto frag_a = [&](int i, int step) -> Frag {
+            if constexpr (AK) {
+                const int row = wm + 32 * i + l32;
+                return E::read_k(ta + row * BKB, (row / 2) % 8, step, h);
+            } else return E::template read_mn<OA::RB>(ta, lane, wm + 32 * i, step);
+        };
+        auto frag_b = [&](int j, int step) -> Frag {
+            if constexpr (BK) {
+                const int row = wn + 32 * j + l32;
+                return E::read_k(tb + row * BKB, (row / 2) % 8, step, h);
+            } else return E::template read_mn<OB::RB>(tb, lane, wn + 32 * j, step);
+        };
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            Frag fa[NB], fb[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) fa[i] = frag_a(i, s);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[j] = frag_b(j, s);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[j], fa[i], acc[i][j]);
+        }
+    };
+
+    const int full = p.Kc / TK, ntiles = (p.Kc + TK - 1) / TK;
+    // K-tile kt goes to buffer kt & 1; only the last one can be partial
+    auto load = [&](int kt) {
+        if (kt < full) {
+            a.template load<false>(p.wa, 0, 0);
+            b.template load<false>(p.wb, 0, 0);
+        } else {
+            a.template load<true>(p.wa, kt * TK, p.Kc);
+            b.template load<true>(p.wb, kt * TK, p.Kc);
+        }
+    };
+    auto store = [&](int kt) {
+        char *t = smem + (kt & 1) * STAGE;
+        if (kt < full) {
+            a.template store<false>(t, 0, 0);
+            b.template store<false>(t + OA::BYTES, 0, 0);
+        } else {
+            a.template store<true>(t, kt * TK, p.Kc);
+            b.template store<true>(t + OA::BYTES, kt * TK, p.Kc);
+        }
+    };
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int kt = 0; kt + 1 < ntiles; ++kt) {
+        load(kt + 1);
+        compute(smem + (kt & 1) * STAGE);
+        store(kt + 1);
+        __syncthreads();
+    }
+    compute(smem + ((ntiles - 1) & 1) * STAGE);
+    __syncthreads();
+
+    // Output.  A lane's accumulator holds row lane % 32 and columns 8 (v / 4) + 4 h + v % 4 of its block
+    // (operands exchanged in the MFMA): one strip of 32 rows at a time goes through LDS as fp32 so that a
+    // lane stores 16 consecutive bytes of a row.
+    char *strip = smem + wave * 32 * STRIP;
+    const int run = p.out_f32 ? 4 : 8;                   // columns per 16-byte store
+    const int lpr = W / run;                             // lanes per row: a power of two
+    const int lcol = (lane % lpr) * run, col = n0 + wn + lcol;
+    float bias[8];
+    const bool has_bias = p.maps.bias != nullptr;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        bias[e] = (has_bias && e < run && col + e < p.No) ? p.maps.bias[axis_offset_fast(p.maps.bias_n, col + e)] : 0.f;
+    const int es = p.out_f32 ? 4 : 2;
+    char *C = p.C + batch * p.sC;
+    const int64_t col_off = col < p.No ? axis_offset_fast(p.maps.c_n, col) : 0;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                f32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = acc[i][j][4 * g + e] * p.alpha;
+                *reinterpret_cast<f32x4 *>(strip + l32 * STRIP + (32 * j + 8 * g + 4 * h) * 4) = w;
+            }
+        __syncthreads();
+        for (int r = lane / lpr; r < 32; r += 64 / lpr) {
+            const int row = m0 + wm + 32 * i + r;
+            if (row >= p.Mo || col >= p.No) continue;
+            const char *src = strip + r * STRIP + lcol * 4;
+            const int64_t row_off = axis_offset_fast(p.maps.c_m, row);
+            float x[8];
+            *reinterpret_cast<f32x4 *>(x) = *reinterpret_cast<const f32x4 *>(src);
+            if (!p.out_f32) *reinterpret_cast<f32x4 *>(x + 4) = *reinterpret_cast<const f32x4 *>(src + 16);
+            if (has_bias) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] += bias[e];
+            }
+            if (p.out_wide) {
+                char *dst = C + (row_off + col_off) * es;
+                if (p.out_f32) *reinterpret_cast<f32x4 *>(dst) = f32x4{x[0], x[1], x[2], x[3]};
+                else *reinterpret_cast<i32x4 *>(dst) = i32x4{(int)pack_bf16x2(x[0], x[1]), (int)pack_bf16x2(x[2], x[3]),
+                                                             (int)pack_bf16x2(x[4], x[5]), (int)pack_bf16x2(x[6], x[7])};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (e < run && col + e < p.No) {
+                        const int64_t at = row_off + axis_offset_fast(p.maps.c_n, col + e);
+                        if (p.out_f32) reinterpret_cast<float *>(C)[at] = x[e];
+                        else reinterpret_cast<unsigned short *>(C)[at] = f32_to_bf16_bits(x[e]);
+                    }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// ---- host side --------------------------------------------------------------------------------------------
+
+template <typename E, int T, int GB> int launch_layout(const GemmArgs &g, const Params &p)
+{
+    const dim3 grid((unsigned)((int64_t)p.tiles_m * p.tiles_n * g.batch)), block(256);
+    if (g.a_kmajor && g.b_kmajor) hipLaunchKernelGGL((gemm_edge_kernel<E, T, GB, true, true>), grid, block, 0, g.stream, p);
+    else if (g.a_kmajor) hipLaunchKernelGGL((gemm_edge_kernel<E, T, GB, true, false>), grid, block, 0, g.stream, p);
+    else hipLaunchKernelGGL((gemm_edge_kernel<E, T, GB, false, false>), grid, block, 0, g.stream, p);
+    return launch_status();
+}
+
+template <typename E, int GB> int launch_tile(const GemmArgs &g, const Params &p, int tile)
+{
+    return tile == 128 ? launch_layout<E, 128, GB>(g, p) : launch_layout<E, 64, GB>(g, p);
+}
+
+}  // namespace edge
+
+// per element type, in a translation unit of its own (piece = bytes per load as chosen by gemm_edge)
+int gemm_edge_bf16(const GemmArgs &g, const edge::Params &p, int tile, int piece);
+int gemm_edge_fp8(const GemmArgs &g, const edge::Params &p, int tile, int piece);
+int gemm_edge_f32(const GemmArgs &g, const edge::Params &p, int tile, int piece);
+
+}  // namespace cube3d

@@ -1,0 +1,115 @@
+// Dispatch of the product kernel for any size (gemm_edge.h).
+#include "gemm_edge.h"
+
+namespace cube3d {
+using namespace edge;
+
+namespace {
+
+constexpr int64_t MAX_EXTENT = (1ll << 31) - 256;   // indices and tile origins stay below 2^31
+
+// widest power of two up to 16 / es elements that divides `x`
+int64_t common_piece(int64_t piece, int64_t x)
+{
+    while (x % piece) piece /= 2;
+    return piece;
+}
+
+// An index that is not cut into shards: one panel longer than any extent.
+AxisMap plain_map(int64_t u)
+{
+    return AxisMap{INT32_MAX, INT32_MAX, 0, 0, u};
+}
+
+// Largest element offset of an operand or of the output (offsets grow with the panel, shard and element numbers).
+int64_t last_offset(const AxisMap &m, int64_t extent)
+{
+    const int64_t blocks = (extent - 1) / m.P1, in_block = blocks ? m.P1 - 1 : extent - 1;
+    const int64_t shards = in_block / m.P2, in_shard = shards ? m.P2 - 1 : in_block;
+    return blocks * m.s1 + shards * m.s2 + in_shard * m.u;
+}
+
+Walk make_walk(const AxisMap &m, int es)
+{
+    Walk w;
+    const int64_t shards = m.P1 / m.P2;
+    w.step = (unsigned)(BKB / es * m.u * es);
+    w.jump2 = (unsigned)((m.s2 - m.P2 * m.u) * es);
+    w.jump1 = (unsigned)((m.s1 - shards * m.s2) * es);
+    w.P2 = m.P2;
+    w.shards = (int)shards;
+    return w;
+}
+
+// elements that can be read at once along the contiguous index `c` of an operand whose other index is `r`
+int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t batch_stride, int64_t widest)
+{
+    if (c.u != 1) return 1;
+    int64_t piece = common_piece(widest, extent);
+    if (c.P2 != INT32_MAX) piece = common_piece(piece, c.P2);
+    for (int64_t x : {c.s1, c.s2, r.s1, r.s2, r.u, batch_stride}) piece = common_piece(piece, x);
+    return piece;
+}
+
+}  // namespace
+
+int gemm_edge(const GemmArgs &g)
+{
+    const int es = g.in_dtype == CUBE3D_F32 ? 4 : g.in_dtype == CUBE3D_BF16 ? 2 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 0;
+    if (es == 0 || (g.out_dtype != CUBE3D_F32 && g.out_dtype != CUBE3D_BF16)) return CUBE3D_ENOTIMPL;
+    if (g.Mo < 1 || g.No < 1 || g.Kc < 1 || g.batch < 1 || (!g.a_kmajor && g.b_kmajor)) return CUBE3D_ENOTIMPL;
+    if (g.Mo > MAX_EXTENT || g.No > MAX_EXTENT || g.Kc > MAX_EXTENT) return CUBE3D_ENOTIMPL;
+    if (g.maps && g.batch != 1) return CUBE3D_ENOTIMPL;
+    if ((g.Mo + 63) / 64 > 65535 || g.batch > 65535) return CUBE3D_ENOTIMPL;   // refused by gemm_generic
+    Params p{};
+    if (g.maps) {
+        p.maps = *g.maps;
+    } else {
+        p.maps.a_mn = plain_map(g.a_kmajor ? g.lda : 1);
+        p.maps.a_k = plain_map(g.a_kmajor ? 1 : g.lda);
+        p.maps.b_mn = plain_map(g.b_kmajor ? g.ldb : 1);
+        p.maps.b_k = plain_map(g.b_kmajor ? 1 : g.ldb);
+        p.maps.c_m = plain_map(g.ldc);
+        p.maps.c_n = p.maps.bias_n = plain_map(1);
+        p.sA = g.strideA * es;
+        p.sB = g.strideB * es;
+    }
+    GemmMaps &m = p.maps;
+    for (AxisMap *x : {&m.a_mn, &m.a_k, &m.b_mn, &m.b_k, &m.c_m, &m.c_n, &m.bias_n}) {
+        if (x->P1 < 1 || x->P2 < 1 || x->P1 % x->P2) return CUBE3D_ENOTIMPL;
+        prepare_axis_map(*x);
+    }
+    // an operand element is buffer start + 32-bit byte offset
+    if ((last_offset(m.a_mn, g.Mo) + last_offset(m.a_k, g.Kc) + 1) * es >= (1ll << 32)) return CUBE3D_ENOTIMPL;
+    if ((last_offset(m.b_mn, g.No) + last_offset(m.b_k, g.Kc) + 1) * es >= (1ll << 32)) return CUBE3D_ENOTIMPL;
+    const int64_t widest = 16 / es;
+    const int64_t pa = g.a_kmajor ? piece_of(m.a_k, m.a_mn, g.Kc, g.maps ? 0 : g.strideA, widest)
+                                  : piece_of(m.a_mn, m.a_k, g.Mo, g.maps ? 0 : g.strideA, widest);
+    const int64_t pb = g.b_kmajor ? piece_of(m.b_k, m.b_mn, g.Kc, g.maps ? 0 : g.strideB, widest)
+                                  : piece_of(m.b_mn, m.b_k, g.No, g.maps ? 0 : g.strideB, widest);
+    const int piece = (int)(pa < pb ? pa : pb) * es;
+    const int oes = g.out_dtype == CUBE3D_F32 ? 4 : 2;
+    p.sC = g.maps ? 0 : g.strideC * oes;
+    p.out_f32 = oes == 4;
+    p.out_wide = piece_of(m.c_n, m.c_m, g.No, g.maps ? 0 : g.strideC, 16 / oes) * oes == 16;
+    p.A = static_cast<const char *>(g.A);
+    p.B = static_cast<const char *>(g.B);
+    p.C = static_cast<char *>(g.C);
+    p.Mo = (int)g.Mo; p.No = (int)g.No; p.Kc = (int)g.Kc;
+    p.alpha = g.alpha;
+    p.wa = make_walk(m.a_k, es);
+    p.wb = make_walk(m.b_k, es);
+    auto tiles = [&](int64_t t) { return ((g.Mo + t - 1) / t) * ((g.No + t - 1) / t) * g.batch; };
+    const int tile = tiles(128) >= num_compute_units() ? 128 : 64;
+    if (tiles(tile) > INT32_MAX / 2) return CUBE3D_ENOTIMPL;
+    p.tiles_m = (int)((g.Mo + tile - 1) / tile);
+    p.tiles_n = (int)((g.No + tile - 1) / tile);
+    p.group_m = 8;
+    switch (g.in_dtype) {
+    case CUBE3D_F32: return gemm_edge_f32(g, p, tile, piece);
+    case CUBE3D_BF16: return gemm_edge_bf16(g, p, tile, piece);
+    default: return gemm_edge_fp8(g, p, tile, piece);
+    }
+}
+
+}  // namespace cube3d
