@@ -3,13 +3,18 @@
 // (gemm_mfma_kernel.h) declines: ragged sizes, few rows, fp32.  The local products of Algorithm 1 step 3 and
 // Algorithm 2 lines 1-2.
 //
-// Work split.  A workgroup of four wavefronts (2 x 2) makes a T x T tile (T = 128 or 64), a wavefront a
-// T/2 x T/2 sub-tile in 32x32 MFMA accumulators.  K-tiles are 128 bytes of the contraction index per row.
-// Operands go through registers into LDS: the loads of K-tile t+1 are issued before the MFMAs of K-tile t
-// and written to the other LDS buffer behind them, one barrier per K-tile, so a load has a whole K-tile of
-// MFMAs, times the workgroups that share the CU, to arrive.  Registers rather than direct-to-LDS loads because
-// a piece may be narrower than 16 bytes, may lie in another shard than its neighbour, and has to be zero
-// beyond the last contraction index.
+// Work split.  A workgroup of four wavefronts makes a T x T tile: T = 128 or 64 as 2 x 2 sub-tiles in 32x32
+// MFMA accumulators, T = 32 as one sub-tile whose k-steps the wavefronts share (few rows and a long contraction:
+// many workgroups and no second pass).  K-tiles are 128 bytes of the contraction index per row.
+// Operands go through registers into LDS, double-buffered, one barrier per K-tile.  Registers rather than
+// direct-to-LDS loads because a piece may be narrower than 16 bytes, may lie in another shard than its
+// neighbour, and has to be zero beyond the last contraction index.
+//
+// What bounds it.  With few workgroups per CU the chain of one K-tile: with one K-tile of loads in flight the
+// wait for them (64 rows x 8192 x 2048 bf16, 32 tiles of 64: 63 us); with four in flight, waits that count
+// exactly one K-tile's loads and fragment reads ahead of the LDS writes 40 us, 25 us with T = 32.  With many
+// workgroups the LDS: a 64 x 64 sub-tile reads 4 KB per 16-deep step of 128 MFMA cycles (6000 x 3000 x 5000 bf16
+// 237 us = 0.76 PFLOP/s; the element-wise kernel it replaced made 30 TFLOP/s on a quarter of that size).
 //
 // Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
 // stored), so only the last, partial K-tile looks at its bounds: it reads element 0 instead and writes zeros.
@@ -20,6 +25,8 @@
 // contraction index as (byte offset, position in the shard, shard in the block): a K-tile step is an add, a
 // compare and, rarely, the jump to the next shard or block; nothing is divided inside the loop.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace cube3d {
@@ -37,7 +44,7 @@ constexpr int BKB = 128;      // bytes of contraction index per K-tile and row
 struct Bf16 {
     static constexpr int ELT = 2, KSTEP = 16;
     typedef i32x4 Frag;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 0; }
     // bytes [16 * slot, +16) of a K-major row hold 8 k: slot 2 * step + h is a fragment
     __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
     {
@@ -65,7 +72,7 @@ struct Bf16 {
 struct Fp8 {
     static constexpr int ELT = 1, KSTEP = 16;
     typedef i32x2 Frag;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : 2 * ((k >> 2) & 1); }
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : 0; }
     __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
     {
         return *reinterpret_cast<const i32x2 *>(row + ((step ^ swz) * 16) + 8 * h);
@@ -88,7 +95,7 @@ struct Fp8 {
 struct F32 {
     static constexpr int ELT = 4, KSTEP = 8;
     typedef f32x4 Frag;
-    __device__ static __forceinline__ int mn_swz(int k, int) { return 8 * ((k >> 2) & 1); }
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 8 * ((k >> 2) & 1) : 0; }
     __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
     {
         return *reinterpret_cast<const f32x4 *>(row + (((2 * step + h) ^ swz) * 16));
@@ -111,7 +118,9 @@ struct F32 {
 };
 
 // Byte distances of an operand's walk along the contraction index.
+enum WalkKind { WALK_ONE_SHARD, WALK_LONG_SHARDS, WALK_SHORT_SHARDS };   // shards at least / less than a K-tile long
 struct Walk {
+    int kind;
     unsigned step;     // one K-tile inside a shard
     unsigned jump2;    // extra when it leaves a shard
     unsigned jump1;    // extra when it leaves a block as well
@@ -156,7 +165,7 @@ template <typename E, int T, int GB, bool KM> struct Operand {
     int pos[NWK], shard[NWK];  // position in the shard, shard in the block
     int kfirst;                // contraction index of walk 0 inside a K-tile
     int lds;                   // LDS byte of slot 0
-    P v[NP * SUB];
+    static constexpr int NV = NP * SUB;
 
     __device__ __forceinline__ void init(const char *b, const AxisMap &mn, const AxisMap &km, const Walk &w, int m0, int extent,
                                          int Kc, int tid)
@@ -183,7 +192,7 @@ template <typename E, int T, int GB, bool KM> struct Operand {
     }
 
     // load K-tile number kt, where the walk stands, then move the walk to the next one
-    template <bool TAIL> __device__ __forceinline__ void load(const Walk &w, int k0, int Kc)
+    template <bool TAIL> __device__ __forceinline__ void load(P (&v)[NV], const Walk &w, int k0, int Kc)
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i)
@@ -193,24 +202,40 @@ template <typename E, int T, int GB, bool KM> struct Operand {
                 if (TAIL) o = k0 + kfirst + (KM ? u * EPP : i * PASS) < Kc ? o : 0;
                 v[i * SUB + u] = *reinterpret_cast<const P *>(base + o);
             }
-        if (!TAIL) {
+        // (the branches are wave-uniform; no load is issued behind one, so that the waits before the LDS
+        // writes stay exact counts)
+#pragma unroll
+        for (int i = 0; i < NWK; ++i) off[i] += w.step;
+        if (w.kind == WALK_ONE_SHARD) return;
+        if (w.kind == WALK_LONG_SHARDS) {
 #pragma unroll
             for (int i = 0; i < NWK; ++i) {
-                off[i] += w.step;
                 pos[i] += TK;
-                while (pos[i] >= w.P2) {
-                    pos[i] -= w.P2;
-                    off[i] += w.jump2;
-                    if (++shard[i] == w.shards) {
-                        shard[i] = 0;
-                        off[i] += w.jump1;
-                    }
+                const bool leaves = pos[i] >= w.P2;
+                pos[i] -= leaves ? w.P2 : 0;
+                off[i] += leaves ? w.jump2 : 0;
+                shard[i] += leaves;
+                const bool block = shard[i] == w.shards;
+                shard[i] = block ? 0 : shard[i];
+                off[i] += block ? w.jump1 : 0;
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < NWK; ++i) {
+            pos[i] += TK;
+            while (pos[i] >= w.P2) {
+                pos[i] -= w.P2;
+                off[i] += w.jump2;
+                if (++shard[i] == w.shards) {
+                    shard[i] = 0;
+                    off[i] += w.jump1;
                 }
             }
         }
     }
 
-    template <bool TAIL> __device__ __forceinline__ void store(char *tile, int k0, int Kc)
+    template <bool TAIL> __device__ __forceinline__ void store(const P (&v)[NV], char *tile, int k0, int Kc) const
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
@@ -225,20 +250,26 @@ template <typename E, int T, int GB, bool KM> struct Operand {
     }
 };
 
+// K-tiles of loads in flight, in registers (T / 4 per lane and K-tile): as many as the accumulators leave
+// room for.  Pieces narrower than a register take one each: one K-tile.
+constexpr int depth(int T, int GB) { return GB < 16 ? 1 : T == 128 ? 2 : 4; }
+
 template <typename E, int T, int GB, bool AK, bool BK>
-__global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_edge_kernel(const Params p)
+__global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_kernel(const Params p)
 {
     typedef Operand<E, T, GB, AK> OA;
     typedef Operand<E, T, GB, BK> OB;
     typedef typename E::Frag Frag;
-    constexpr int TK = OA::TK, STEPS = TK / E::KSTEP, W = T / 2, NB = W / 32;
+    constexpr int KW = T == 32 ? 4 : 1;                 // wavefronts that share a sub-tile, each with its own k-steps
+    constexpr int TK = OA::TK, STEPS = TK / E::KSTEP, W = KW == 1 ? T / 2 : T, NB = W / 32, D = depth(T, GB);
     constexpr int STAGE = OA::BYTES + OB::BYTES;
     constexpr int STRIP = W * 4 + 16;                   // bytes of a staged output row (fp32, padded)
-    static_assert(4 * 32 * STRIP <= 2 * STAGE, "the output strips reuse the K-tile buffers");
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+    constexpr int LDS = 2 * STAGE > 4 * 32 * STRIP ? 2 * STAGE : 4 * 32 * STRIP;   // the strips reuse the K-tile buffers
+    static_assert(STEPS % KW == 0, "whole k-steps per wavefront");
+    __shared__ __attribute__((aligned(1024))) char smem[LDS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = (wave >> 1) * W, wn = (wave & 1) * W, h = lane >> 5, l32 = lane & 31;
+    const int wm = KW == 1 ? (wave >> 1) * W : 0, wn = KW == 1 ? (wave & 1) * W : 0, h = lane >> 5, l32 = lane & 31;
 
     // Workgroup ids go round robin over the 8 XCDs: hand every XCD one contiguous run of tiles, so that the
     // panels its workgroups share come through one L2.
@@ -253,6 +284,8 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_edge_kernel(const 
     OB b;
     a.init(p.A + batch * p.sA, p.maps.a_mn, p.maps.a_k, p.wa, m0, p.Mo, p.Kc, tid);
     b.init(p.B + batch * p.sB, p.maps.b_mn, p.maps.b_k, p.wb, n0, p.No, p.Kc, tid);
+    typename OA::P va[D][OA::NV];
+    typename OB::P vb[D][OB::NV];
 
     f32x16 acc[NB][NB];
 #pragma unroll
@@ -262,70 +295,96 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_edge_kernel(const 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    auto compute = [&](const char *ta) {
+    auto frag_a = [&](const char *ta, int i, int step) -> Frag {
+        if constexpr (AK) {
+            const int row = wm + 32 * i + l32;
+            return E::read_k(ta + row * BKB, (row / 2) % 8, step, h);
+        } else return E::template read_mn<OA::RB>(ta, lane, wm + 32 * i, step);
+    };
+    auto frag_b = [&](const char *ta, int j, int step) -> Frag {
         const char *tb = ta + OA::BYTES;
-        auto frag_a = [&](int i, int step) -> Frag {
-            if constexpr (AK) {
-                const int row = wm + 32 * i + l32;
-                return E::read_k(ta + row * BKB, (row / 2) % 8, step, h);
-            } else return E::template read_mn<OA::RB>(ta, lane, wm + 32 * i, step);
+        if constexpr (BK) {
+            const int row = wn + 32 * j + l32;
+            return E::read_k(tb + row * BKB, (row / 2) % 8, step, h);
+        } else return E::template read_mn<OB::RB>(tb, lane, wn + 32 * j, step);
+    };
+    // The MFMAs of one K-tile, with `moves` (the LDS writes and loads of later K-tiles) behind the fragment
+    // reads of the first EARLY steps: a wavefront that is alone on its SIMD has its MFMAs wait for those
+    // reads only, and not for the writes.
+    constexpr int MY_STEPS = STEPS / KW, EARLY = T == 128 ? 1 : MY_STEPS < 4 ? MY_STEPS : 4;
+    auto compute = [&](const char *ta, auto &&moves) {
+        Frag fa[EARLY][NB], fb[EARLY][NB];
+        auto step_no = [&](int s) { return KW == 1 ? s : wave * MY_STEPS + s; };
+        auto read = [&](int s) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) fa[s % EARLY][i] = frag_a(ta, i, step_no(s));
+#pragma unroll
+            for (int j = 0; j < NB; ++j) fb[s % EARLY][j] = frag_b(ta, j, step_no(s));
         };
-        auto frag_b = [&](int j, int step) -> Frag {
-            if constexpr (BK) {
-                const int row = wn + 32 * j + l32;
-                return E::read_k(tb + row * BKB, (row / 2) % 8, step, h);
-            } else return E::template read_mn<OB::RB>(tb, lane, wn + 32 * j, step);
-        };
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            Frag fa[NB], fb[NB];
+        for (int s = 0; s < EARLY; ++s) read(s);
+        moves();
 #pragma unroll
-            for (int i = 0; i < NB; ++i) fa[i] = frag_a(i, s);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) fb[j] = frag_b(j, s);
+        for (int s = 0; s < MY_STEPS; ++s) {
+            if (s >= EARLY) read(s);
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[j], fa[i], acc[i][j]);
+                for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[s % EARLY][j], fa[s % EARLY][i], acc[i][j]);
         }
     };
 
     const int full = p.Kc / TK, ntiles = (p.Kc + TK - 1) / TK;
-    // K-tile kt goes to buffer kt & 1; only the last one can be partial
-    auto load = [&](int kt) {
-        if (kt < full) {
-            a.template load<false>(p.wa, 0, 0);
-            b.template load<false>(p.wb, 0, 0);
-        } else {
-            a.template load<true>(p.wa, kt * TK, p.Kc);
-            b.template load<true>(p.wb, kt * TK, p.Kc);
-        }
+    // K-tile kt travels in register set kt % D and sits in LDS buffer kt & 1.  The loop proper takes only
+    // whole K-tiles and has no branch around a load, so that each wait covers one K-tile's loads and leaves the
+    // younger ones in flight; the last K-tiles look at every piece's bounds (beyond the last one they load
+    // element 0 and write zeros).
+    auto load = [&](auto tail, int d, int kt) {
+        a.template load<tail.value>(va[d], p.wa, kt * TK, p.Kc);
+        b.template load<tail.value>(vb[d], p.wb, kt * TK, p.Kc);
     };
-    auto store = [&](int kt) {
+    auto store = [&](auto tail, int d, int kt) {
         char *t = smem + (kt & 1) * STAGE;
-        if (kt < full) {
-            a.template store<false>(t, 0, 0);
-            b.template store<false>(t + OA::BYTES, 0, 0);
-        } else {
-            a.template store<true>(t, kt * TK, p.Kc);
-            b.template store<true>(t + OA::BYTES, kt * TK, p.Kc);
-        }
+        a.template store<tail.value>(va[d], t, kt * TK, p.Kc);
+        b.template store<tail.value>(vb[d], t + OA::BYTES, kt * TK, p.Kc);
     };
-    load(0);
-    store(0);
+    const std::integral_constant<bool, false> whole{};
+    const std::integral_constant<bool, true> tail{};
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(tail, d, d);
+    store(tail, 0, 0);
+    load(tail, 0, D);
     __syncthreads();
-    for (int kt = 0; kt + 1 < ntiles; ++kt) {
-        load(kt + 1);
-        compute(smem + (kt & 1) * STAGE);
-        store(kt + 1);
-        __syncthreads();
+    int k0 = 0;
+    for (; k0 + 2 * D < full; k0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            // (the buffer of K-tile kt + 1 was last read before the previous barrier)
+            const int kt = k0 + d;
+            compute(smem + (kt & 1) * STAGE, [&] {
+                store(whole, (d + 1) % D, kt + 1);
+                load(whole, (d + 1) % D, kt + 1 + D);
+            });
+            __syncthreads();
+        }
     }
-    compute(smem + ((ntiles - 1) & 1) * STAGE);
-    __syncthreads();
+    for (; k0 < ntiles; k0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int kt = k0 + d;
+            if (kt < ntiles)
+                compute(smem + (kt & 1) * STAGE, [&] {
+                    store(tail, (d + 1) % D, kt + 1);
+                    load(tail, (d + 1) % D, kt + 1 + D);
+                });
+            __syncthreads();
+        }
+    }
 
     // Output.  A lane's accumulator holds row lane % 32 and columns 8 (v / 4) + 4 h + v % 4 of its block
     // (operands exchanged in the MFMA): one strip of 32 rows at a time goes through LDS as fp32 so that a
-    // lane stores 16 consecutive bytes of a row.
+    // lane stores 16 consecutive bytes of a row.  Where four wavefronts share the sub-tile their strips are
+    // added in ascending order, each wavefront a quarter of the rows.
     char *strip = smem + wave * 32 * STRIP;
     const int run = p.out_f32 ? 4 : 8;                   // columns per 16-byte store
     const int lpr = W / run;                             // lanes per row: a power of two
@@ -346,21 +405,25 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_edge_kernel(const 
             for (int g = 0; g < 4; ++g) {
                 f32x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = acc[i][j][4 * g + e] * p.alpha;
+                for (int e = 0; e < 4; ++e) w[e] = acc[i][j][4 * g + e];
                 *reinterpret_cast<f32x4 *>(strip + l32 * STRIP + (32 * j + 8 * g + 4 * h) * 4) = w;
             }
         __syncthreads();
-        for (int r = lane / lpr; r < 32; r += 64 / lpr) {
+        const int r_first = KW == 1 ? 0 : wave * (32 / KW), r_end = r_first + 32 / KW;
+        for (int r = r_first + lane / lpr; r < r_end; r += 64 / lpr) {
             const int row = m0 + wm + 32 * i + r;
             if (row >= p.Mo || col >= p.No) continue;
-            const char *src = strip + r * STRIP + lcol * 4;
             const int64_t row_off = axis_offset_fast(p.maps.c_m, row);
             float x[8];
-            *reinterpret_cast<f32x4 *>(x) = *reinterpret_cast<const f32x4 *>(src);
-            if (!p.out_f32) *reinterpret_cast<f32x4 *>(x + 4) = *reinterpret_cast<const f32x4 *>(src + 16);
-            if (has_bias) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] += bias[e];
+            for (int half = 0; half < 2; ++half) {
+                if (half && p.out_f32) break;
+                const char *src = (KW == 1 ? strip : smem) + r * STRIP + lcol * 4 + half * 16;
+                f32x4 t = *reinterpret_cast<const f32x4 *>(src);
+#pragma unroll
+                for (int k = 1; k < KW; ++k) t += *reinterpret_cast<const f32x4 *>(src + k * 32 * STRIP);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[4 * half + e] = t[e] * p.alpha + bias[4 * half + e];
             }
             if (p.out_wide) {
                 char *dst = C + (row_off + col_off) * es;
@@ -394,7 +457,10 @@ template <typename E, int T, int GB> int launch_layout(const GemmArgs &g, const 
 
 template <typename E, int GB> int launch_tile(const GemmArgs &g, const Params &p, int tile)
 {
-    return tile == 128 ? launch_layout<E, 128, GB>(g, p) : launch_layout<E, 64, GB>(g, p);
+    if constexpr (GB > 1) {     // (single bytes: the pieces of a 128 x 128 tile don't fit the registers)
+        if (tile == 128) return launch_layout<E, 128, GB>(g, p);
+    }
+    return tile == 32 ? launch_layout<E, 32, GB>(g, p) : launch_layout<E, 64, GB>(g, p);
 }
 
 }  // namespace edge

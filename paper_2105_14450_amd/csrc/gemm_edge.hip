@@ -6,7 +6,7 @@ using namespace edge;
 
 namespace {
 
-constexpr int64_t MAX_EXTENT = (1ll << 31) - 256;   // indices and tile origins stay below 2^31
+constexpr int64_t MAX_EXTENT = (1ll << 31) - 4096;   // indices stay below 2^31, also those of the K-tiles in flight at the end
 
 // widest power of two up to 16 / es elements that divides `x`
 int64_t common_piece(int64_t piece, int64_t x)
@@ -29,7 +29,7 @@ int64_t last_offset(const AxisMap &m, int64_t extent)
     return blocks * m.s1 + shards * m.s2 + in_shard * m.u;
 }
 
-Walk make_walk(const AxisMap &m, int es)
+Walk make_walk(const AxisMap &m, int64_t Kc, int es)
 {
     Walk w;
     const int64_t shards = m.P1 / m.P2;
@@ -37,6 +37,7 @@ Walk make_walk(const AxisMap &m, int es)
     w.jump2 = (unsigned)((m.s2 - m.P2 * m.u) * es);
     w.jump1 = (unsigned)((m.s1 - shards * m.s2) * es);
     w.P2 = m.P2;
+    w.kind = Kc <= m.P2 ? WALK_ONE_SHARD : m.P2 >= BKB / es ? WALK_LONG_SHARDS : WALK_SHORT_SHARDS;
     w.shards = (int)shards;
     return w;
 }
@@ -97,10 +98,17 @@ int gemm_edge(const GemmArgs &g)
     p.C = static_cast<char *>(g.C);
     p.Mo = (int)g.Mo; p.No = (int)g.No; p.Kc = (int)g.Kc;
     p.alpha = g.alpha;
-    p.wa = make_walk(m.a_k, es);
-    p.wb = make_walk(m.b_k, es);
+    p.wa = make_walk(m.a_k, g.Kc, es);
+    p.wb = make_walk(m.b_k, g.Kc, es);
     auto tiles = [&](int64_t t) { return ((g.Mo + t - 1) / t) * ((g.No + t - 1) / t) * g.batch; };
-    const int tile = tiles(128) >= num_compute_units() ? 128 : 64;
+    // Tile side: the largest that still gives most CUs a tile, because a CU without one costs more than the
+    // smaller tile's extra LDS reads.  bf16, us with 128 / 64 / 32 at (Mo, No, Kc): (2997, 1152, 4608) = 216 tiles
+    // of 128: 55 / 67 / 94; (3000, 1024, 4096) = 192: 50 / 48 / 73; (1000, 2048, 1024) = 128, fp8: 16 / 12 / 20;
+    // with 64: (384, 1536, 999) = 144 tiles of 64: 19 / 11.5 / 13.1; (64, 8192, 2048) = 128: 30 / 17.0 / 16.7;
+    // (999, 384, 1536) = 96: 24 / 12.6 / 10.9; (64, 2048, 8192) = 32: 91 / 40 / 25.
+    const int64_t cus = num_compute_units();
+    const bool single_bytes = piece < 4 && es == 1;      // no 128 x 128 kernel, see launch_tile
+    const int tile = tiles(128) > cus * 3 / 4 && !single_bytes ? 128 : tiles(64) > cus / 2 ? 64 : 32;
     if (tiles(tile) > INT32_MAX / 2) return CUBE3D_ENOTIMPL;
     p.tiles_m = (int)((g.Mo + tile - 1) / tile);
     p.tiles_n = (int)((g.No + tile - 1) / tile);

@@ -1,0 +1,61 @@
+"""Products of any size (GPU) against the oracle: edges of the 32 / 64 / 128 tiles, partial K-tiles, every width of a
+load piece, plain blocks and a cube of shards read in place.  Integers in [-4, 4]: all sums are exact, so every
+result is compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2105_14450_amd as c3
+from oracle import matmul as om
+from oracle import numfmt
+from oracle.layout import Cube
+from paper_2105_14450_amd import synth
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(q, M, K, N, dtype, out, seed):
+    inp = synth.linear_inputs(M, K, N, dtype, "int", seed)
+    val = {k: numfmt.decode(raw, dtype, scale) for k, (raw, scale) in inp.items()}
+    d = c3.make_desc(q, M, K, N, in_dtype=gu.CODE[dtype], out_dtype=gu.CODE[out], shard_dtype=gu.CODE[out],
+                     scale_x=inp["X"][1], scale_w=inp["W"][1], scale_dy=inp["dY"][1])
+    ref = om.forward(val["X"], val["W"], 4), om.backward_dx(val["dY"], val["W"], 4), om.backward_dw(val["X"], val["dY"], 4)
+    return inp, d, [numfmt.round_to(r, out) for r in ref]
+
+
+# pieces of 16 bytes (multiples of 16), 8 or 4 bytes, single elements; sizes below, at and above a tile and a K-tile;
+# many tiles of 128, some of 64, few of 32; contractions of one partial K-tile up to more than the pipeline's depth
+@pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16")])
+@pytest.mark.parametrize("M,K,N", [(1, 1, 1), (31, 16, 33), (33, 48, 80), (64, 656, 144), (65, 4, 130), (100, 130, 36),
+                                   (127, 97, 129), (130, 336, 1040), (257, 1008, 272), (999, 24, 2064), (1700, 272, 2050)])
+def test_blocks(M, K, N, dtype, out):
+    inp, d, ref = _setup(1, M, K, N, dtype, out, 1000 + M)
+    X, W, G = (gu.to_device(inp[k][0]) for k in ("X", "W", "dY"))
+    P, Q, R = gu.empty((M, N), out), gu.empty((M, K), out), gu.empty((K, N), out)
+    c3.cube3d_linear_fwd(d, (0, 0, 0), X, W, P, gu.workspace(d, c3.OP_FWD, False))
+    c3.cube3d_linear_bwd_dx(d, (0, 0, 0), G, W, Q, gu.workspace(d, c3.OP_BWD_DX, False))
+    c3.cube3d_linear_bwd_dw(d, (0, 0, 0), X, G, R, gu.workspace(d, c3.OP_BWD_DW, False))
+    torch.cuda.synchronize()
+    for got, want, name in zip((P, Q, R), ref, ("P", "Q", "R")):
+        assert np.array_equal(gu.to_host(got, out), want), "%s %dx%dx%d %s" % (name, M, K, N, dtype)
+
+
+# shards shorter than a K-tile, shards that end inside one, blocks of several K-tiles; narrow and wide pieces
+@pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("f32", "f32"), ("fp8_e4m3", "bf16")])
+@pytest.mark.parametrize("q,M,K,N", [(2, 12, 6, 4), (2, 68, 160, 192), (3, 333, 144, 288), (3, 9 * 37, 3 * 130, 9 * 34),
+                                     (4, 16 * 5, 4 * 336, 16 * 48), (2, 4 * 300, 2 * 400, 4 * 208)])
+def test_cube_in_place(q, M, K, N, dtype, out):
+    inp, d, ref = _setup(q, M, K, N, dtype, out, 2000 + M)
+    cube, n = Cube(q, M, K, N, "y"), q ** 3
+    x, w, g = (gu.to_device(np.ascontiguousarray(cut(inp[k][0]))) for k, cut in
+               (("X", cube.shard_x), ("W", cube.shard_w), ("dY", cube.shard_y)))
+    y, dx, dw = (gu.empty(s, out) for s in ((n, cube.Ms, cube.Nb), (n, cube.Ms, cube.Kb), (n, cube.Kb, cube.Ns)))
+    c3.virtual_cube_linear_fwd(d, x, w, None, y)
+    c3.virtual_cube_linear_bwd_dx(d, g, w, dx)
+    c3.virtual_cube_linear_bwd_dw(d, x, g, dw)
+    torch.cuda.synchronize()
+    for got, cut, want, name in zip((y, dx, dw), (cube.shard_y, cube.shard_x, cube.shard_w), ref, ("Y", "dX", "dW")):
+        want = cut(want)
+        assert np.array_equal(gu.to_host(got, out).reshape(want.shape), want), "%s q=%d %dx%dx%d %s" % (name, q, M, K, N, dtype)
