@@ -63,7 +63,8 @@ struct Bf16 {
         const i32x2 lo = rd(ad), hi = rd(ad + 4 * RB);
         return Frag{lo[0], lo[1], hi[0], hi[1]};
     }
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    static constexpr int MFMAS = 1;      // MFMAs per fragment pair
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
@@ -86,7 +87,8 @@ struct Fp8 {
         return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
             (__attribute__((address_space(3))) i32x2 *)(__attribute__((address_space(3))) const char *)ad);
     }
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    static constexpr int MFMAS = 1;      // MFMAs per fragment pair
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int)
     {
         return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(__builtin_bit_cast(long, a), __builtin_bit_cast(long, b), c, 0, 0, 0);
     }
@@ -109,11 +111,10 @@ struct F32 {
         for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const float *>(ad + i * RB);
         return f;
     }
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c)
+    static constexpr int MFMAS = 4;
+    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int i)
     {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
-        return c;
+        return __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
     }
 };
 
@@ -312,6 +313,7 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
     // reads of the first EARLY steps: a wavefront that is alone on its SIMD has its MFMAs wait for those
     // reads only, and not for the writes.
     constexpr int MY_STEPS = STEPS / KW, EARLY = T == 128 ? 1 : MY_STEPS < 4 ? MY_STEPS : 4;
+    constexpr bool MOVES_LAST = T == 128;
     auto compute = [&](const char *ta, auto &&moves) {
         Frag fa[EARLY][NB], fb[EARLY][NB];
         auto step_no = [&](int s) { return KW == 1 ? s : wave * MY_STEPS + s; };
@@ -323,15 +325,18 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
         };
 #pragma unroll
         for (int s = 0; s < EARLY; ++s) read(s);
-        moves();
+        if constexpr (!MOVES_LAST) moves();
 #pragma unroll
         for (int s = 0; s < MY_STEPS; ++s) {
             if (s >= EARLY) read(s);
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
+            for (int x = 0; x < E::MFMAS; ++x)      // (consecutive MFMAs on different accumulators where there are several)
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[s % EARLY][j], fa[s % EARLY][i], acc[i][j]);
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[s % EARLY][j], fa[s % EARLY][i], acc[i][j], x);
         }
+        if constexpr (MOVES_LAST) moves();
     };
 
     const int full = p.Kc / TK, ntiles = (p.Kc + TK - 1) / TK;
