@@ -21,9 +21,9 @@
 // An operand is read in pieces of GB bytes: the widest power of two, up to 16, that divides every distance and
 // extent along the contiguous index, so no piece straddles a row, a shard or the buffer's end.
 //
-// Address arithmetic.  Plain operands are a map with one endless panel.  A lane keeps the walk along the
-// contraction index as (byte offset, position in the shard, shard in the block): a K-tile step is an add, a
-// compare and, rarely, the jump to the next shard or block; nothing is divided inside the loop.
+// Address arithmetic.  Plain operands are a map with one endless panel.  From one K-tile to the next all of a
+// lane's byte offsets grow by one distance; only where a shard ends are they taken from the index map again (with
+// multiplications, nothing is divided), so a K-tile costs one vector addition per load.
 #pragma once
 #include <type_traits>
 
@@ -118,16 +118,6 @@ struct F32 {
     }
 };
 
-// Byte distances of an operand's walk along the contraction index.
-enum WalkKind { WALK_ONE_SHARD, WALK_LONG_SHARDS, WALK_SHORT_SHARDS };   // shards at least / less than a K-tile long
-struct Walk {
-    int kind;
-    unsigned step;     // one K-tile inside a shard
-    unsigned jump2;    // extra when it leaves a shard
-    unsigned jump1;    // extra when it leaves a block as well
-    int P2, shards;    // shard length, shards per block
-};
-
 struct Params {
     const char *A, *B;
     char *C;
@@ -137,7 +127,7 @@ struct Params {
     float alpha;
     int out_f32, out_wide;         // out_wide: 16-byte runs of output columns are aligned and lie in one shard
     GemmMaps maps;
-    Walk wa, wb;
+    unsigned step_a, step_b;       // bytes from one K-tile to the next inside a shard
 };
 
 template <int GB> struct Piece;
@@ -160,16 +150,28 @@ template <typename E, int T, int GB, bool KM> struct Operand {
     static constexpr int NST = KM ? NP : SUB, NWK = KM ? SUB : NP;
     static constexpr int BYTES = T * BKB;
 
-    const char *base;
-    unsigned st[NST];          // byte offset of the output index
-    unsigned off[NWK];         // byte offset of the contraction index
-    int pos[NWK], shard[NWK];  // position in the shard, shard in the block
-    int kfirst;                // contraction index of walk 0 inside a K-tile
-    int lds;                   // LDS byte of slot 0
     static constexpr int NV = NP * SUB;
 
-    __device__ __forceinline__ void init(const char *b, const AxisMap &mn, const AxisMap &km, const Walk &w, int m0, int extent,
-                                         int Kc, int tid)
+    const char *base;
+    unsigned st[NST];          // byte offset of the output index
+    unsigned o[NV];            // byte offset of the pieces of the K-tile that starts at k
+    int k, in_shard;           // wave-uniform: that K-tile's first contraction index, its position in its shard
+    int kfirst;                // contraction index of walk 0 inside a K-tile
+    int lds;                   // LDS byte of slot 0
+
+    __device__ __forceinline__ void place(const AxisMap &km, int Kc)
+    {
+        in_shard = k - (int)(((uint64_t)(unsigned)k * km.M2) >> km.N2) * km.P2;
+#pragma unroll
+        for (int w = 0; w < NWK; ++w) {
+            // (beyond Kc the offset is not used)
+            const unsigned off = (unsigned)(axis_offset_fast(km, min(k + kfirst + w * (KM ? EPP : PASS), Kc - 1)) * E::ELT);
+#pragma unroll
+            for (int s = 0; s < NST; ++s) o[KM ? s * SUB + w : w * SUB + s] = st[s] + off;
+        }
+    }
+
+    __device__ __forceinline__ void init(const char *b, const AxisMap &mn, const AxisMap &km, int m0, int extent, int Kc, int tid)
     {
         base = b;
         const int row = tid / SPR, slot = tid % SPR;
@@ -182,58 +184,29 @@ template <typename E, int T, int GB, bool KM> struct Operand {
             const int x = KM ? min(m0 + row + i * PASS, extent - 1) : min(m0 + slot * EPS + i * EPP, extent - EPP);
             st[i] = (unsigned)(axis_offset_fast(mn, x) * E::ELT);
         }
-#pragma unroll
-        for (int i = 0; i < NWK; ++i) {
-            const int k = min(kfirst + i * (KM ? EPP : PASS), Kc - 1);   // (beyond Kc the walk is not used)
-            off[i] = (unsigned)(axis_offset_fast(km, k) * E::ELT);
-            const unsigned hi = (unsigned)(((uint64_t)(unsigned)k * km.M1) >> km.N1), r1 = k - hi * km.P1;
-            shard[i] = (int)(((uint64_t)r1 * km.M2) >> km.N2);
-            pos[i] = r1 - shard[i] * w.P2;
-        }
+        k = 0;
+        place(km, Kc);
     }
 
-    // load K-tile number kt, where the walk stands, then move the walk to the next one
-    template <bool TAIL> __device__ __forceinline__ void load(P (&v)[NV], const Walk &w, int k0, int Kc)
+    // Load the K-tile that starts at k, then move on to the next one.  Unless a shard ends inside these two
+    // K-tiles every piece moves by the same distance; the branch is wave-uniform and has no load behind it,
+    // so that the waits before the LDS writes stay exact counts.
+    template <bool TAIL> __device__ __forceinline__ void load(P (&v)[NV], const AxisMap &km, unsigned step, int Kc)
     {
 #pragma unroll
         for (int i = 0; i < NP; ++i)
 #pragma unroll
             for (int u = 0; u < SUB; ++u) {
-                unsigned o = KM ? st[i] + off[u] : st[u] + off[i];
-                if (TAIL) o = k0 + kfirst + (KM ? u * EPP : i * PASS) < Kc ? o : 0;
-                v[i * SUB + u] = *reinterpret_cast<const P *>(base + o);
+                unsigned at = o[i * SUB + u];
+                if (TAIL) at = k + kfirst + (KM ? u * EPP : i * PASS) < Kc ? at : 0;
+                v[i * SUB + u] = *reinterpret_cast<const P *>(base + at);
             }
-        // (the branches are wave-uniform; no load is issued behind one, so that the waits before the LDS
-        // writes stay exact counts)
+        k += TK;
+        if (in_shard + 2 * TK <= km.P2) {
+            in_shard += TK;
 #pragma unroll
-        for (int i = 0; i < NWK; ++i) off[i] += w.step;
-        if (w.kind == WALK_ONE_SHARD) return;
-        if (w.kind == WALK_LONG_SHARDS) {
-#pragma unroll
-            for (int i = 0; i < NWK; ++i) {
-                pos[i] += TK;
-                const bool leaves = pos[i] >= w.P2;
-                pos[i] -= leaves ? w.P2 : 0;
-                off[i] += leaves ? w.jump2 : 0;
-                shard[i] += leaves;
-                const bool block = shard[i] == w.shards;
-                shard[i] = block ? 0 : shard[i];
-                off[i] += block ? w.jump1 : 0;
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < NWK; ++i) {
-            pos[i] += TK;
-            while (pos[i] >= w.P2) {
-                pos[i] -= w.P2;
-                off[i] += w.jump2;
-                if (++shard[i] == w.shards) {
-                    shard[i] = 0;
-                    off[i] += w.jump1;
-                }
-            }
-        }
+            for (int i = 0; i < NV; ++i) o[i] += step;
+        } else place(km, Kc);
     }
 
     template <bool TAIL> __device__ __forceinline__ void store(const P (&v)[NV], char *tile, int k0, int Kc) const
@@ -283,8 +256,8 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
 
     OA a;
     OB b;
-    a.init(p.A + batch * p.sA, p.maps.a_mn, p.maps.a_k, p.wa, m0, p.Mo, p.Kc, tid);
-    b.init(p.B + batch * p.sB, p.maps.b_mn, p.maps.b_k, p.wb, n0, p.No, p.Kc, tid);
+    a.init(p.A + batch * p.sA, p.maps.a_mn, p.maps.a_k, m0, p.Mo, p.Kc, tid);
+    b.init(p.B + batch * p.sB, p.maps.b_mn, p.maps.b_k, n0, p.No, p.Kc, tid);
     typename OA::P va[D][OA::NV];
     typename OB::P vb[D][OB::NV];
 
@@ -344,21 +317,23 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
     // whole K-tiles and has no branch around a load, so that each wait covers one K-tile's loads and leaves the
     // younger ones in flight; the last K-tiles look at every piece's bounds (beyond the last one they load
     // element 0 and write zeros).
-    auto load = [&](auto tail, int d, int kt) {
-        a.template load<tail.value>(va[d], p.wa, kt * TK, p.Kc);
-        b.template load<tail.value>(vb[d], p.wb, kt * TK, p.Kc);
+    auto load = [&](auto tail, int d) {
+        a.template load<tail.value>(va[d], p.maps.a_k, p.step_a, p.Kc);
+        b.template load<tail.value>(vb[d], p.maps.b_k, p.step_b, p.Kc);
     };
+    // (an even number of K-tiles per pass: buffer and LDS addresses are constants)
+    auto buffer = [&](int d, int kt) { return smem + (D % 2 == 0 ? d & 1 : kt & 1) * STAGE; };
     auto store = [&](auto tail, int d, int kt) {
-        char *t = smem + (kt & 1) * STAGE;
+        char *t = buffer(d, kt);
         a.template store<tail.value>(va[d], t, kt * TK, p.Kc);
         b.template store<tail.value>(vb[d], t + OA::BYTES, kt * TK, p.Kc);
     };
     const std::integral_constant<bool, false> whole{};
     const std::integral_constant<bool, true> tail{};
 #pragma unroll
-    for (int d = 0; d < D; ++d) load(tail, d, d);
+    for (int d = 0; d < D; ++d) load(tail, d);
     store(tail, 0, 0);
-    load(tail, 0, D);
+    load(tail, 0);
     __syncthreads();
     int k0 = 0;
     for (; k0 + 2 * D < full; k0 += D) {
@@ -366,9 +341,9 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
         for (int d = 0; d < D; ++d) {
             // (the buffer of K-tile kt + 1 was last read before the previous barrier)
             const int kt = k0 + d;
-            compute(smem + (kt & 1) * STAGE, [&] {
+            compute(buffer(d, kt), [&] {
                 store(whole, (d + 1) % D, kt + 1);
-                load(whole, (d + 1) % D, kt + 1 + D);
+                load(whole, (d + 1) % D);
             });
             __syncthreads();
         }
@@ -378,9 +353,9 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
         for (int d = 0; d < D; ++d) {
             const int kt = k0 + d;
             if (kt < ntiles)
-                compute(smem + (kt & 1) * STAGE, [&] {
+                compute(buffer(d, kt), [&] {
                     store(tail, (d + 1) % D, kt + 1);
-                    load(tail, (d + 1) % D, kt + 1 + D);
+                    load(tail, (d + 1) % D);
                 });
             __syncthreads();
         }

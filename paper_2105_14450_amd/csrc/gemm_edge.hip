@@ -29,19 +29,6 @@ int64_t last_offset(const AxisMap &m, int64_t extent)
     return blocks * m.s1 + shards * m.s2 + in_shard * m.u;
 }
 
-Walk make_walk(const AxisMap &m, int64_t Kc, int es)
-{
-    Walk w;
-    const int64_t shards = m.P1 / m.P2;
-    w.step = (unsigned)(BKB / es * m.u * es);
-    w.jump2 = (unsigned)((m.s2 - m.P2 * m.u) * es);
-    w.jump1 = (unsigned)((m.s1 - shards * m.s2) * es);
-    w.P2 = m.P2;
-    w.kind = Kc <= m.P2 ? WALK_ONE_SHARD : m.P2 >= BKB / es ? WALK_LONG_SHARDS : WALK_SHORT_SHARDS;
-    w.shards = (int)shards;
-    return w;
-}
-
 // elements that can be read at once along the contiguous index `c` of an operand whose other index is `r`
 int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t batch_stride, int64_t widest)
 {
@@ -98,8 +85,8 @@ int gemm_edge(const GemmArgs &g)
     p.C = static_cast<char *>(g.C);
     p.Mo = (int)g.Mo; p.No = (int)g.No; p.Kc = (int)g.Kc;
     p.alpha = g.alpha;
-    p.wa = make_walk(m.a_k, g.Kc, es);
-    p.wb = make_walk(m.b_k, g.Kc, es);
+    p.step_a = (unsigned)(BKB * m.a_k.u);
+    p.step_b = (unsigned)(BKB * m.b_k.u);
     auto tiles = [&](int64_t t) { return ((g.Mo + t - 1) / t) * ((g.No + t - 1) / t) * g.batch; };
     // Tile side: the largest that still gives most CUs a tile, because a CU without one costs more than the
     // smaller tile's extra LDS reads.  bf16, us with 128 / 64 / 32 at (Mo, No, Kc): (2997, 1152, 4608) = 216 tiles
