@@ -146,7 +146,9 @@ __device__ __forceinline__ RowMap map_copy_row(const CubeGeom &g, int mode, int 
 // VecT = what one lane moves per step; es = element size in bytes.  A wavefront works on the
 // four rows it owns in its block at the same time, four pieces per row in flight, so that every
 // lane has up to sixteen independent loads outstanding before the first store (the rows are
-// short: one row alone leaves the memory system idle).
+// short: one row alone leaves the memory system idle).  Streaming stores: at 168 MB moved by
+// two scatters and two assembles 57.0 -> 53.9 us, at 470 MB 123 -> 113 us; the same time at 0.4-19 MB, where launches
+// count.
 template <typename VecT>
 __global__ __launch_bounds__(256) void cube_copy_kernel(CubeGeom g, int mode, int64_t rows, int nseg, int es,
                                                         const char *__restrict__ src, char *__restrict__ dst)
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(256) void cube_copy_kernel(CubeGeom g, int mode, in
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t c = c0 + 64 * u;
-                if (c < total && row0 + 4 * w < rows) d[w][c] = v[w][u];
+                if (c < total && row0 + 4 * w < rows) __builtin_nontemporal_store(v[w][u], d[w] + c);
             }
     }
 }
