@@ -10,11 +10,12 @@
 // direct-to-LDS loads because a piece may be narrower than 16 bytes, may lie in another shard than its
 // neighbour, and has to be zero beyond the last contraction index.
 //
-// What bounds it.  With few workgroups per CU the chain of one K-tile: with one K-tile of loads in flight the
-// wait for them (64 rows x 8192 x 2048 bf16, 32 tiles of 64: 63 us); with four in flight, waits that count
-// exactly one K-tile's loads and fragment reads ahead of the LDS writes 40 us, 25 us with T = 32.  With many
-// workgroups the LDS: a 64 x 64 sub-tile reads 4 KB per 16-deep step of 128 MFMA cycles (6000 x 3000 x 5000 bf16
-// 237 us = 0.76 PFLOP/s; the element-wise kernel it replaced made 30 TFLOP/s on a quarter of that size).
+// What bounds it.  With few workgroups per CU the chain of one K-tile: 64 rows x 8192 x 2048 bf16 took 63 us on 32
+// tiles of 64 with one K-tile of loads in flight; four in flight, waits that count exactly one K-tile's loads and
+// fragment reads ahead of the LDS writes made it 40, the 32 x 32 tiles 25, one vector addition per load in place of a
+// per-lane walk 22 (33 MB of weights: 5 us at 7 TB/s).  With many workgroups LDS reads and vector instructions share
+// the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 237 us = 0.76 PFLOP/s, three fp8 products of
+// 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel that took these sizes before made 30-45 TFLOP/s.
 //
 // Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
 // stored), so only the last, partial K-tile looks at its bounds: it reads element 0 instead and writes zeros.

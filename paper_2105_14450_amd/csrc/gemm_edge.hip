@@ -91,7 +91,7 @@ int gemm_edge(const GemmArgs &g)
     // Tile side: the largest that still gives most CUs a tile, because a CU without one costs more than the
     // smaller tile's extra LDS reads.  bf16, us with 128 / 64 / 32 at (Mo, No, Kc): (2997, 1152, 4608) = 216 tiles
     // of 128: 55 / 67 / 94; (3000, 1024, 4096) = 192: 50 / 48 / 73; (1000, 2048, 1024) = 128, fp8: 16 / 12 / 20;
-    // with 64: (384, 1536, 999) = 144 tiles of 64: 19 / 11.5 / 13.1; (64, 8192, 2048) = 128: 30 / 17.0 / 16.7;
+    // with 64: (384, 1536, 999) = 144 tiles of 64: 19 / 11.5 / 13.1; (64, 8192, 2048) = 128: 29 / 17.0 / 16.7;
     // (999, 384, 1536) = 96: 24 / 12.6 / 10.9; (64, 2048, 8192) = 32: 91 / 40 / 25.
     const int64_t cus = num_compute_units();
     const bool single_bytes = piece < 4 && es == 1;      // no 128 x 128 kernel, see launch_tile
