@@ -4,16 +4,18 @@
 // Algorithm 2 lines 1-2.
 //
 // Work split.  A workgroup of four wavefronts makes a T x T tile: T = 128 or 64 as 2 x 2 sub-tiles in 32x32
-// MFMA accumulators, T = 32 as one sub-tile whose k-steps the wavefronts share (few rows and a long contraction:
-// many workgroups and no second pass).  K-tiles are 128 bytes of the contraction index per row.
+// MFMA accumulators, T = 32 as 2 x 2 blocks of 16x16 MFMAs (bf16, fp8) or as one block whose k-steps the wavefronts
+// share (fp32), for few rows: many workgroups and no second pass.  K-tiles are 128 bytes of the contraction index per row.
 // Operands go through registers into LDS, double-buffered, one barrier per K-tile.  Registers rather than
 // direct-to-LDS loads because a piece may be narrower than 16 bytes, may lie in another shard than its
 // neighbour, and has to be zero beyond the last contraction index.
 //
 // What bounds it.  With few workgroups per CU the chain of one K-tile: 64 rows x 8192 x 2048 bf16 took 63 us on 32
 // tiles of 64 with one K-tile of loads in flight; four in flight, waits that count exactly one K-tile's loads and
-// fragment reads ahead of the LDS writes made it 40, the 32 x 32 tiles 25, one vector addition per load in place of a
-// per-lane walk 22 (33 MB of weights: 5 us at 7 TB/s).  With many workgroups LDS reads and vector instructions share
+// fragment reads ahead of the LDS writes made it 40, the 32 x 32 tiles and one vector addition per load in place of a
+// per-lane walk 26 (33 MB of weights: 5 us at 7 TB/s).  32 x 32 tiles whose wavefronts shared the k-steps, as in
+// fp32, took 22 there and 23 against 26 for 64 x 2048 x 8192 with W^T, but 7.2 against 6.7 for 64 x 512 x 512, and their four
+// partial sums made a row's bits depend on how many rows the call had.  With many workgroups LDS reads and vector instructions share
 // the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 237 us = 0.76 PFLOP/s, three fp8 products of
 // 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel that took these sizes before made 30-45 TFLOP/s.
 //
@@ -38,85 +40,160 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BKB = 128;      // bytes of contraction index per K-tile and row
 
-// Element traits.  A step is what one LDS fragment covers: KSTEP contraction indices, lane half h holding
-// [h * KSTEP / 2, (h + 1) * KSTEP / 2) of them for both kinds of operand.
+// Element traits.  M32 and M16 are the matrix instructions on 32 x 32 and 16 x 16 blocks: a step is what one
+// LDS fragment covers, KSTEP contraction indices of which the lane groups (lane / SIDE) hold consecutive runs, the same
+// for both kinds of operand.  In bf16 and fp8 every output element adds its products in ascending order in one
+// accumulator, and M16 gives the bits of M32 (compared on random operands over 512 indices): a row of the
+// result does not depend on the tile side, that is on how many other rows the call has.
 //   mn_swz: slot permutation of an MN-major row (spr 16-byte slots) in k-row k, so that the k-rows that one
 //   read covers lie in different banks
 struct Bf16 {
-    static constexpr int ELT = 2, KSTEP = 16;
-    typedef i32x4 Frag;
+    static constexpr int ELT = 2;
     __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 0; }
-    // bytes [16 * slot, +16) of a K-major row hold 8 k: slot 2 * step + h is a fragment
-    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
+    struct M32 {
+        static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;      // MFMAS: MFMAs per fragment pair
+        typedef i32x4 Frag;
+        typedef f32x16 Acc;
+        // bytes [16 * slot, +16) of a K-major row hold 8 k: slot 2 * step + group is a fragment
+        __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
+        {
+            return *reinterpret_cast<const i32x4 *>(row + (((2 * step + g) ^ swz) * 16));
+        }
+        // transposing reads: 16 lanes take 4 k-rows x 16 columns, lane n receives the 4 k of column n
+        template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+        {
+            const int g = lane / 16;
+            return read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0 + 16 * (g % 2), 8 * (g / 2));
+        }
+        __device__ static __forceinline__ Acc mfma(Frag a, Frag b, Acc c, int)
+        {
+            return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        }
+    };
+    struct M16 {
+        static constexpr int SIDE = 16, KSTEP = 32, MFMAS = 1;
+        typedef i32x4 Frag;
+        typedef f32x4 Acc;
+        __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
+        {
+            return *reinterpret_cast<const i32x4 *>(row + (((4 * step + g) ^ swz) * 16));
+        }
+        template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+        {
+            return read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0, 8 * (lane / 16));
+        }
+        __device__ static __forceinline__ Acc mfma(Frag a, Frag b, Acc c, int)
+        {
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        }
+    };
+    // 8 k from k-row k0 on (a multiple of 8) of 16 columns, for the 16 lanes s of a group
+    template <int RB> __device__ static __forceinline__ i32x4 read_mn_at(const char *tile, int s, int col0, int k0)
     {
-        return *reinterpret_cast<const i32x4 *>(row + (((2 * step + h) ^ swz) * 16));
-    }
-    // transposing reads: 16 lanes take 4 k-rows x 16 columns, lane n receives the 4 k of column n
-    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
-    {
-        const int g = lane / 16, s = lane % 16;
-        const int k = 8 * (g / 2) + s / 4, byte = (col0 + 16 * (g % 2) + 4 * (s % 4)) * 2;
-        const char *ad = tile + (step * KSTEP + k) * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
+        const int k = k0 + s / 4, byte = (col0 + 4 * (s % 4)) * 2;
+        const char *ad = tile + k * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
         auto rd = [](const char *a) {
             return __builtin_bit_cast(i32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                 (__attribute__((address_space(3))) s16x4 *)(__attribute__((address_space(3))) const char *)a));
         };
         const i32x2 lo = rd(ad), hi = rd(ad + 4 * RB);
-        return Frag{lo[0], lo[1], hi[0], hi[1]};
-    }
-    static constexpr int MFMAS = 1;      // MFMAs per fragment pair
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+        return i32x4{lo[0], lo[1], hi[0], hi[1]};
     }
 };
 
 struct Fp8 {
-    static constexpr int ELT = 1, KSTEP = 16;
-    typedef i32x2 Frag;
+    static constexpr int ELT = 1;
     __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : 0; }
-    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
+    struct M32 {
+        static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;
+        typedef i32x2 Frag;
+        typedef f32x16 Acc;
+        __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
+        {
+            return *reinterpret_cast<const i32x2 *>(row + ((step ^ swz) * 16) + 8 * g);
+        }
+        template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+        {
+            const int g = lane / 16;
+            return read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0 + 16 * (g % 2), 8 * (g / 2));
+        }
+        __device__ static __forceinline__ Acc mfma(Frag a, Frag b, Acc c, int)
+        {
+            return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(__builtin_bit_cast(long, a), __builtin_bit_cast(long, b), c, 0, 0, 0);
+        }
+    };
+    struct M16 {
+        static constexpr int SIDE = 16, KSTEP = 32, MFMAS = 1;
+        typedef i32x2 Frag;
+        typedef f32x4 Acc;
+        __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
+        {
+            return *reinterpret_cast<const i32x2 *>(row + (((2 * step + g / 2) ^ swz) * 16) + 8 * (g % 2));
+        }
+        template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+        {
+            return read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0, 8 * (lane / 16));
+        }
+        __device__ static __forceinline__ Acc mfma(Frag a, Frag b, Acc c, int)
+        {
+            return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(__builtin_bit_cast(long, a), __builtin_bit_cast(long, b), c, 0, 0, 0);
+        }
+    };
+    // transposing read: 16 lanes take 8 k-rows x 16 columns, lane n receives the 8 k of column n
+    template <int RB> __device__ static __forceinline__ i32x2 read_mn_at(const char *tile, int s, int col0, int k0)
     {
-        return *reinterpret_cast<const i32x2 *>(row + ((step ^ swz) * 16) + 8 * h);
-    }
-    // transposing reads: 16 lanes take 8 k-rows x 16 columns, lane n receives the 8 k of column n
-    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
-    {
-        const int g = lane / 16, s = lane % 16;
-        const int k = 8 * (g / 2) + s / 2, byte = col0 + 16 * (g % 2) + 8 * (s % 2);
-        const char *ad = tile + (step * KSTEP + k) * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
+        const int k = k0 + s / 2, byte = col0 + 8 * (s % 2);
+        const char *ad = tile + k * RB + (((byte / 16) ^ mn_swz(k, RB / 16)) * 16) + byte % 16;
         return __builtin_amdgcn_ds_read_tr8_b64_v2i32(
             (__attribute__((address_space(3))) i32x2 *)(__attribute__((address_space(3))) const char *)ad);
-    }
-    static constexpr int MFMAS = 1;      // MFMAs per fragment pair
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_fp8_fp8(__builtin_bit_cast(long, a), __builtin_bit_cast(long, b), c, 0, 0, 0);
     }
 };
 
 struct F32 {
-    static constexpr int ELT = 4, KSTEP = 8;
-    typedef f32x4 Frag;
+    static constexpr int ELT = 4;
     __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 8 * ((k >> 2) & 1) : 0; }
-    __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int h)
-    {
-        return *reinterpret_cast<const f32x4 *>(row + (((2 * step + h) ^ swz) * 16));
-    }
-    template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
-    {
-        const int h = lane / 32, byte = (col0 + lane % 32) * 4;
-        const char *ad = tile + (step * KSTEP + 4 * h) * RB + (((byte / 16) ^ mn_swz(4 * h, RB / 16)) * 16) + byte % 16;
-        Frag f;
+    struct M32 {
+        static constexpr int SIDE = 32, KSTEP = 8, MFMAS = 4;
+        typedef f32x4 Frag;
+        typedef f32x16 Acc;
+        __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
+        {
+            return *reinterpret_cast<const f32x4 *>(row + (((2 * step + g) ^ swz) * 16));
+        }
+        template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
+        {
+            const int h = lane / 32, byte = (col0 + lane % 32) * 4;
+            const char *ad = tile + (step * KSTEP + 4 * h) * RB + (((byte / 16) ^ mn_swz(4 * h, RB / 16)) * 16) + byte % 16;
+            Frag f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const float *>(ad + i * RB);
-        return f;
-    }
-    static constexpr int MFMAS = 4;
-    __device__ static __forceinline__ f32x16 mfma(Frag a, Frag b, f32x16 c, int i)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
-    }
+            for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const float *>(ad + i * RB);
+            return f;
+        }
+        __device__ static __forceinline__ Acc mfma(Frag a, Frag b, Acc c, int i)
+        {
+            return __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
+        }
+    };
+};
+
+// How the four wavefronts make a 32 x 32 tile.  bf16, fp8: a 16 x 16 block each, so that an element's sum stays one chain.
+// fp32: the whole tile each, over a quarter of the k-steps, the four partial sums added at the end: an MFMA
+// takes twice as long for a sixteenth of the products, and the shorter chains' error is no larger.
+template <typename E, int T> struct Instr {
+    typedef typename E::M32 M;
+    static constexpr int KW = 1;
+};
+template <> struct Instr<Bf16, 32> {
+    typedef Bf16::M16 M;
+    static constexpr int KW = 1;
+};
+template <> struct Instr<Fp8, 32> {
+    typedef Fp8::M16 M;
+    static constexpr int KW = 1;
+};
+template <> struct Instr<F32, 32> {
+    typedef F32::M32 M;
+    static constexpr int KW = 4;
 };
 
 struct Params {
@@ -234,17 +311,19 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
 {
     typedef Operand<E, T, GB, AK> OA;
     typedef Operand<E, T, GB, BK> OB;
-    typedef typename E::Frag Frag;
-    constexpr int KW = T == 32 ? 4 : 1;                 // wavefronts that share a sub-tile, each with its own k-steps
-    constexpr int TK = OA::TK, STEPS = TK / E::KSTEP, W = KW == 1 ? T / 2 : T, NB = W / 32, D = depth(T, GB);
+    typedef typename Instr<E, T>::M M;
+    typedef typename M::Frag Frag;
+    typedef typename M::Acc Acc;
+    constexpr int SIDE = M::SIDE, VALS = SIDE * SIDE / 64;      // an accumulator block and a lane's values of it
+    constexpr int TK = OA::TK, STEPS = TK / M::KSTEP, KW = Instr<E, T>::KW, W = KW == 1 ? T / 2 : T, NB = W / SIDE, D = depth(T, GB);
     constexpr int STAGE = OA::BYTES + OB::BYTES;
     constexpr int STRIP = W * 4 + 16;                   // bytes of a staged output row (fp32, padded)
-    constexpr int LDS = 2 * STAGE > 4 * 32 * STRIP ? 2 * STAGE : 4 * 32 * STRIP;   // the strips reuse the K-tile buffers
+    constexpr int LDS = 2 * STAGE > 4 * SIDE * STRIP ? 2 * STAGE : 4 * SIDE * STRIP;   // the strips reuse the K-tile buffers
     static_assert(STEPS % KW == 0, "whole k-steps per wavefront");
     __shared__ __attribute__((aligned(1024))) char smem[LDS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = KW == 1 ? (wave >> 1) * W : 0, wn = KW == 1 ? (wave & 1) * W : 0, h = lane >> 5, l32 = lane & 31;
+    const int wm = KW == 1 ? (wave >> 1) * W : 0, wn = KW == 1 ? (wave & 1) * W : 0, g = lane / SIDE, in_side = lane % SIDE;
 
     // Workgroup ids go round robin over the 8 XCDs: hand every XCD one contiguous run of tiles, so that the
     // panels its workgroups share come through one L2.
@@ -262,26 +341,26 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
     typename OA::P va[D][OA::NV];
     typename OB::P vb[D][OB::NV];
 
-    f32x16 acc[NB][NB];
+    Acc acc[NB][NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < VALS; ++v) acc[i][j][v] = 0.f;
 
     auto frag_a = [&](const char *ta, int i, int step) -> Frag {
         if constexpr (AK) {
-            const int row = wm + 32 * i + l32;
-            return E::read_k(ta + row * BKB, (row / 2) % 8, step, h);
-        } else return E::template read_mn<OA::RB>(ta, lane, wm + 32 * i, step);
+            const int row = wm + SIDE * i + in_side;
+            return M::read_k(ta + row * BKB, (row / 2) % 8, step, g);
+        } else return M::template read_mn<OA::RB>(ta, lane, wm + SIDE * i, step);
     };
     auto frag_b = [&](const char *ta, int j, int step) -> Frag {
         const char *tb = ta + OA::BYTES;
         if constexpr (BK) {
-            const int row = wn + 32 * j + l32;
-            return E::read_k(tb + row * BKB, (row / 2) % 8, step, h);
-        } else return E::template read_mn<OB::RB>(tb, lane, wn + 32 * j, step);
+            const int row = wn + SIDE * j + in_side;
+            return M::read_k(tb + row * BKB, (row / 2) % 8, step, g);
+        } else return M::template read_mn<OB::RB>(tb, lane, wn + SIDE * j, step);
     };
     // The MFMAs of one K-tile, with `moves` (the LDS writes and loads of later K-tiles) behind the fragment
     // reads of the first EARLY steps: a wavefront that is alone on its SIMD has its MFMAs wait for those
@@ -304,11 +383,11 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
         for (int s = 0; s < MY_STEPS; ++s) {
             if (s >= EARLY) read(s);
 #pragma unroll
-            for (int x = 0; x < E::MFMAS; ++x)      // (consecutive MFMAs on different accumulators where there are several)
+            for (int x = 0; x < M::MFMAS; ++x)      // (consecutive MFMAs on different accumulators where there are several)
 #pragma unroll
                 for (int i = 0; i < NB; ++i)
 #pragma unroll
-                    for (int j = 0; j < NB; ++j) acc[i][j] = E::mfma(fb[s % EARLY][j], fa[s % EARLY][i], acc[i][j], x);
+                    for (int j = 0; j < NB; ++j) acc[i][j] = M::mfma(fb[s % EARLY][j], fa[s % EARLY][i], acc[i][j], x);
         }
         if constexpr (MOVES_LAST) moves();
     };
@@ -362,11 +441,11 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
         }
     }
 
-    // Output.  A lane's accumulator holds row lane % 32 and columns 8 (v / 4) + 4 h + v % 4 of its block
-    // (operands exchanged in the MFMA): one strip of 32 rows at a time goes through LDS as fp32 so that a
-    // lane stores 16 consecutive bytes of a row.  Where four wavefronts share the sub-tile their strips are
+    // Output.  A lane's accumulator holds row lane % SIDE and columns 8 (v / 4) + 4 (lane / SIDE) + v % 4 of its
+    // block (operands exchanged in the MFMA): one strip of SIDE rows at a time goes through LDS as fp32 so that
+    // a lane stores 16 consecutive bytes of a row.  Where four wavefronts share the tile their strips are
     // added in ascending order, each wavefront a quarter of the rows.
-    char *strip = smem + wave * 32 * STRIP;
+    char *strip = smem + wave * SIDE * STRIP;
     const int run = p.out_f32 ? 4 : 8;                   // columns per 16-byte store
     const int lpr = W / run;                             // lanes per row: a power of two
     const int lcol = (lane % lpr) * run, col = n0 + wn + lcol;
@@ -383,16 +462,16 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int v = 0; v < VALS; v += 4) {
                 f32x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = acc[i][j][4 * g + e];
-                *reinterpret_cast<f32x4 *>(strip + l32 * STRIP + (32 * j + 8 * g + 4 * h) * 4) = w;
+                for (int e = 0; e < 4; ++e) w[e] = acc[i][j][v + e];
+                *reinterpret_cast<f32x4 *>(strip + in_side * STRIP + (SIDE * j + 2 * v + 4 * g) * 4) = w;
             }
         __syncthreads();
-        const int r_first = KW == 1 ? 0 : wave * (32 / KW), r_end = r_first + 32 / KW;
+        const int r_first = KW == 1 ? 0 : wave * (SIDE / KW), r_end = r_first + SIDE / KW;
         for (int r = r_first + lane / lpr; r < r_end; r += 64 / lpr) {
-            const int row = m0 + wm + 32 * i + r;
+            const int row = m0 + wm + SIDE * i + r;
             if (row >= p.Mo || col >= p.No) continue;
             const int64_t row_off = axis_offset_fast(p.maps.c_m, row);
             float x[8];
@@ -402,7 +481,7 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
                 const char *src = (KW == 1 ? strip : smem) + r * STRIP + lcol * 4 + half * 16;
                 f32x4 t = *reinterpret_cast<const f32x4 *>(src);
 #pragma unroll
-                for (int k = 1; k < KW; ++k) t += *reinterpret_cast<const f32x4 *>(src + k * 32 * STRIP);
+                for (int k = 1; k < KW; ++k) t += *reinterpret_cast<const f32x4 *>(src + k * SIDE * STRIP);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[4 * half + e] = t[e] * p.alpha + bias[4 * half + e];
             }

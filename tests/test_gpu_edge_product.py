@@ -59,3 +59,27 @@ def test_cube_in_place(q, M, K, N, dtype, out):
     for got, cut, want, name in zip((y, dx, dw), (cube.shard_y, cube.shard_x, cube.shard_w), ref, ("Y", "dX", "dW")):
         want = cut(want)
         assert np.array_equal(gu.to_host(got, out).reshape(want.shape), want), "%s q=%d %dx%dx%d %s" % (name, q, M, K, N, dtype)
+
+
+# bf16 and fp8: every element adds its products in ascending order in one accumulator, whatever the tile, so the rows of a small
+# call are bit for bit those of a large one.  33 x 1040 outputs run on 32 x 32 tiles, 400 x 1600 on 64 x 64, 1808 x 1600
+# on 128 x 128.
+@pytest.mark.parametrize("dtype,out", [("bf16", "f32"), ("bf16", "bf16"), ("fp8_e4m3", "f32")])
+@pytest.mark.parametrize("k", [40, 488, 2000, 1001])
+@pytest.mark.parametrize("form", [c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB])
+def test_same_bits_for_every_number_of_rows(form, k, dtype, out):
+    m, n = (1808, 1600) if k % 8 == 0 else (1811, 1601)
+    inp = synth.linear_inputs(m, k, n, dtype, "normal", 3000 + k)
+    A, B = gu.to_device(inp["X"][0]), gu.to_device(inp["W"][0])                # [m, k], [k, n]
+    results = []
+    for rows, cols in ((m, n), (400, n), (33, n - 560)):
+        a = (A[:rows].t() if form == c3.FORM_ATB else A[:rows]).contiguous()
+        b = (B[:, :cols].t() if form == c3.FORM_ABT else B[:, :cols]).contiguous()
+        mm = c3.make_matmul(1, form, rows, cols, k, in_dtype=gu.CODE[dtype], out_dtype=gu.CODE[out])
+        results.append(gu.empty((rows, cols), out))
+        c3.cube3d_matmul_blocks(mm, a, b, results[-1])
+    torch.cuda.synchronize()
+    whole = gu.raw_host(results[0])
+    for small in map(gu.raw_host, results[1:]):
+        rows, cols = small.shape
+        assert np.array_equal(small.view(np.uint8), np.ascontiguousarray(whole[:rows, :cols]).view(np.uint8)), small.shape
