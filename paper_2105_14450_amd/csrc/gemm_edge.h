@@ -208,6 +208,14 @@ struct Params {
     unsigned step_a, step_b;       // bytes from one K-tile to the next inside a shard
 };
 
+// What a product runs on: the tile side, the bytes per load that its sizes and distances allow (the kernels exist for
+// 16, 4 and one element's), the kernel's arguments.  CUBE3D_ENOTIMPL: left to gemm_generic.
+struct Plan {
+    int tile, piece;
+    Params params;
+};
+int make_plan(const GemmArgs &g, Plan *plan);
+
 template <int GB> struct Piece;
 template <> struct Piece<16> { typedef i32x4 Type; };
 template <> struct Piece<8> { typedef i32x2 Type; };

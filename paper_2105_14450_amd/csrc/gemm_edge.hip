@@ -39,9 +39,14 @@ int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t bat
     return piece;
 }
 
+// A launch has fewer than 2^32 work-items along a grid dimension: 2^24 workgroups of 256.
+constexpr int64_t MAX_WORKGROUPS = (1ll << 24) - 1;
+
 }  // namespace
 
-int gemm_edge(const GemmArgs &g)
+namespace edge {
+
+int make_plan(const GemmArgs &g, Plan *plan)
 {
     const int es = g.in_dtype == CUBE3D_F32 ? 4 : g.in_dtype == CUBE3D_BF16 ? 2 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 0;
     if (es == 0 || (g.out_dtype != CUBE3D_F32 && g.out_dtype != CUBE3D_BF16)) return CUBE3D_ENOTIMPL;
@@ -49,7 +54,8 @@ int gemm_edge(const GemmArgs &g)
     if (g.Mo > MAX_EXTENT || g.No > MAX_EXTENT || g.Kc > MAX_EXTENT) return CUBE3D_ENOTIMPL;
     if (g.maps && g.batch != 1) return CUBE3D_ENOTIMPL;
     if ((g.Mo + 63) / 64 > 65535 || g.batch > 65535) return CUBE3D_ENOTIMPL;   // refused by gemm_generic
-    Params p{};
+    Params &p = plan->params;
+    p = Params{};
     if (g.maps) {
         p.maps = *g.maps;
     } else {
@@ -75,7 +81,7 @@ int gemm_edge(const GemmArgs &g)
                                   : piece_of(m.a_mn, m.a_k, g.Mo, g.maps ? 0 : g.strideA, widest);
     const int64_t pb = g.b_kmajor ? piece_of(m.b_k, m.b_mn, g.Kc, g.maps ? 0 : g.strideB, widest)
                                   : piece_of(m.b_mn, m.b_k, g.No, g.maps ? 0 : g.strideB, widest);
-    const int piece = (int)(pa < pb ? pa : pb) * es;
+    const int piece = plan->piece = (int)(pa < pb ? pa : pb) * es;
     const int oes = g.out_dtype == CUBE3D_F32 ? 4 : 2;
     p.sC = g.maps ? 0 : g.strideC * oes;
     p.out_f32 = oes == 4;
@@ -95,15 +101,25 @@ int gemm_edge(const GemmArgs &g)
     // (999, 384, 1536) = 96: 24 / 12.6 / 10.9; (64, 2048, 8192) = 32: 91 / 40 / 25.
     const int64_t cus = num_compute_units();
     const bool single_bytes = piece < 4 && es == 1;      // no 128 x 128 kernel, see launch_tile
-    const int tile = tiles(128) > cus * 3 / 4 && !single_bytes ? 128 : tiles(64) > cus / 2 ? 64 : 32;
-    if (tiles(tile) > INT32_MAX / 2) return CUBE3D_ENOTIMPL;
+    const int tile = plan->tile = tiles(128) > cus * 3 / 4 && !single_bytes ? 128 : tiles(64) > cus / 2 ? 64 : 32;
+    if (tiles(tile) > MAX_WORKGROUPS) return CUBE3D_ENOTIMPL;
     p.tiles_m = (int)((g.Mo + tile - 1) / tile);
     p.tiles_n = (int)((g.No + tile - 1) / tile);
     p.group_m = 8;
+    return CUBE3D_OK;
+}
+
+}  // namespace edge
+
+int gemm_edge(const GemmArgs &g)
+{
+    Plan plan;
+    const int rc = make_plan(g, &plan);
+    if (rc != CUBE3D_OK) return rc;
     switch (g.in_dtype) {
-    case CUBE3D_F32: return gemm_edge_f32(g, p, tile, piece);
-    case CUBE3D_BF16: return gemm_edge_bf16(g, p, tile, piece);
-    default: return gemm_edge_fp8(g, p, tile, piece);
+    case CUBE3D_F32: return gemm_edge_f32(g, plan.params, plan.tile, plan.piece);
+    case CUBE3D_BF16: return gemm_edge_bf16(g, plan.params, plan.tile, plan.piece);
+    default: return gemm_edge_fp8(g, plan.params, plan.tile, plan.piece);
     }
 }
 

@@ -83,3 +83,15 @@ def test_same_bits_for_every_number_of_rows(form, k, dtype, out):
     for small in map(gu.raw_host, results[1:]):
         rows, cols = small.shape
         assert np.array_equal(small.view(np.uint8), np.ascontiguousarray(whole[:rows, :cols]).view(np.uint8)), small.shape
+
+
+# 64000 blocks of 1 x 33600: more 64 x 64 tiles than one grid dimension holds
+def test_very_many_thin_blocks():
+    q, n = 40, 33600
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    a = torch.randint(-4, 5, (q ** 3, 1), device="cuda", generator=gen, dtype=torch.int8).to(torch.bfloat16)
+    b = torch.randint(-4, 5, (q ** 3, n), device="cuda", generator=gen, dtype=torch.int8).to(torch.bfloat16)
+    c = torch.full((q ** 3, n), float("nan"), device="cuda", dtype=torch.bfloat16)
+    mm = c3.make_matmul(q, c3.FORM_AB, 1, n, 1, in_dtype=c3.BF16, out_dtype=c3.BF16)
+    c3.cube3d_matmul_blocks(mm, a, b, c)
+    assert torch.equal(c, b.mul_(a))            # products of integers up to 4: exact
