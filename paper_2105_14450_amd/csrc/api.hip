@@ -104,7 +104,7 @@ size_t workspace_for(const GemmArgs &a)
     return gemm_fast_workspace(a);
 }
 
-// The first kernel family that takes the product: tile-aligned sizes, then any size, then operands of 4 GB and more.
+// The first kernel family that takes the product: tile-aligned sizes, then any size, then element by element.
 int run_gemm(const GemmArgs &a)
 {
     int rc = gemm_fast(a);

@@ -115,7 +115,8 @@ struct GemmArgs {
 // Any shape, any supported dtype; bounds-checked.  Returns a cube3d_status.
 int gemm_generic(const GemmArgs &g);
 
-// Any size and dtype whose operands span less than 4 GB; CUBE3D_ENOTIMPL otherwise.
+// Any size and dtype; CUBE3D_ENOTIMPL where gemm_generic is faster (short contractions) or has to take it: operands that
+// span 4 GB or more, 2^24 tiles or more; also what gemm_generic refuses (more than 64 * 65535 rows, 65535 blocks).
 int gemm_edge(const GemmArgs &g);
 
 // Tuned bf16 / fp8 path; returns CUBE3D_ENOTIMPL when the shape does not fit its tiles.

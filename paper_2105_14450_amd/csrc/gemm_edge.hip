@@ -39,6 +39,49 @@ int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t bat
     return piece;
 }
 
+// Estimated time of a launch in us, to compare this kernel with the element-wise one (gemm_generic) where the contraction is
+// short: a workgroup here pays for its pipeline's start and its staged output however few K-tiles it has, an element-wise
+// one next to nothing besides its steps of 32.  Fitted to 1700 products of 1-4096 blocks with a contraction of 1-640
+// on one MI355X, all kernels timed at each; over 2450 products the choice is 1.2 % slower than the best one in the
+// mean, and at 55 of them more than 5 % slower than the element-wise kernel (at most 1.46 times; without it at 1120, up to 8 times).
+//   start: launch, first loads, output;  tile, ktile: per workgroup and per K-tile of it when all CUs are busy
+struct Cost {
+    float start, tile, ktile;
+};
+constexpr Cost COST[8][3] = {
+    // tiles of 32                64                    128
+    {{5.25f, 0.47f, 0.06f}, {5.68f, 1.15f, 0.28f}, {9.66f, 2.12f, 0.76f}},      // bf16, loads of 16 bytes
+    {{6.10f, 0.57f, 0.19f}, {8.03f, 0.90f, 0.55f}, {17.0f, 4.08f, 1.35f}},      //       4
+    {{6.77f, 0.67f, 0.41f}, {9.13f, 1.11f, 1.03f}, {19.0f, 3.40f, 2.88f}},      //       2
+    {{5.29f, 0.50f, 0.05f}, {5.47f, 1.23f, 0.25f}, {9.69f, 2.19f, 0.84f}},      // fp8, loads of 16 bytes
+    {{6.03f, 0.63f, 0.16f}, {7.82f, 1.03f, 0.48f}, {13.1f, 4.15f, 1.48f}},      //      4
+    {{7.59f, 0.94f, 1.04f}, {8.92f, 2.79f, 2.38f}, {8.92f, 2.79f, 2.38f}},      //      1 (no tiles of 128)
+    {{5.44f, 0.84f, 0.18f}, {6.56f, 1.26f, 0.65f}, {11.6f, 3.54f, 2.17f}},      // fp32, loads of 16 bytes
+    {{5.83f, 0.84f, 0.24f}, {8.74f, 1.09f, 0.78f}, {17.4f, 5.00f, 2.69f}},      //       4
+};
+//   least: workgroups per CU below which a launch gets no faster;  step, full: per step of 32, and more of it the fuller
+//   the tiles are (elements beyond the edges are not loaded)
+struct ElementCost {
+    float start, least, step, full;
+};
+constexpr ElementCost ELEMENT_COST[3] = {{4.79f, 2.44f, 0.43f, 0.53f}, {4.82f, 2.56f, 0.41f, 0.44f}, {4.74f, 1.69f, 0.85f, 0.68f}};
+constexpr float ELEMENT_MAPS = 3.f;      // an index map divides four times per element: 2.4-3.2 times a step's time
+constexpr int64_t SHORT = 640;           // beyond, its steps leave the caches and the fit; bytes read singly (fp8) cross at about
+                                         // 1000-2000: 3001 x 3001 x 1025, 286 here against 253 us
+
+bool element_wise_is_faster(const GemmArgs &g, int tile, int piece, int64_t workgroups, int64_t workgroups64)
+{
+    if (g.Kc > SHORT) return false;
+    const int type = g.in_dtype == CUBE3D_BF16 ? 0 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 2, es = type == 0 ? 2 : type == 1 ? 1 : 4;
+    const Cost &c = COST[3 * type + (piece >= 16 ? 0 : piece >= 4 ? 1 : 2)][tile == 32 ? 0 : tile == 64 ? 1 : 2];
+    const ElementCost &e = ELEMENT_COST[type];
+    const float cus = (float)num_compute_units(), per_cu = (float)workgroups / cus, per_cu64 = (float)workgroups64 / cus;
+    const float full = (float)((double)g.Mo * (double)g.No * g.batch / ((double)workgroups64 * 64 * 64));
+    const float here = c.start + (per_cu > 1.f ? per_cu : 1.f) * (c.tile + c.ktile * (float)((g.Kc * es + BKB - 1) / BKB));
+    const float steps = (float)((g.Kc + 31) / 32) * (g.maps ? ELEMENT_MAPS : 1.f);
+    return e.start + (per_cu64 > e.least ? per_cu64 : e.least) * steps * (e.step + e.full * full) < here;
+}
+
 // A launch has fewer than 2^32 work-items along a grid dimension: 2^24 workgroups of 256.
 constexpr int64_t MAX_WORKGROUPS = (1ll << 24) - 1;
 
@@ -99,9 +142,13 @@ int make_plan(const GemmArgs &g, Plan *plan)
     // of 128: 55 / 67 / 94; (3000, 1024, 4096) = 192: 50 / 48 / 73; (1000, 2048, 1024) = 128, fp8: 16 / 12 / 20;
     // with 64: (384, 1536, 999) = 144 tiles of 64: 19 / 11.5 / 13.1; (64, 8192, 2048) = 128: 29 / 17.0 / 16.7;
     // (999, 384, 1536) = 96: 24 / 12.6 / 10.9; (64, 2048, 8192) = 32: 91 / 40 / 25.
-    const int64_t cus = num_compute_units();
+    // And not where most of the larger tile lies beyond the output: it takes the time of two to three half as wide.
+    // 4096 blocks, bf16: 41 x 41 x 1025 684 / 370 / 662, 41 x 41 x 129 151 / 70 / 130, 9 x 9 x 1025 481 / 222 / 120,
+    // 24 x 104 x 1032 224 / 250 / 304; 512 of 101 x 201 x 257 82 / 122 / 220; fp8, 304 x 528 x 144 121 / 162 / 253.
+    const int64_t cus = num_compute_units(), t32 = tiles(32), t64 = tiles(64), t128 = tiles(128);
     const bool single_bytes = piece < 4 && es == 1;      // no 128 x 128 kernel, see launch_tile
-    const int tile = plan->tile = tiles(128) > cus * 3 / 4 && !single_bytes ? 128 : tiles(64) > cus / 2 ? 64 : 32;
+    const int tile = plan->tile = t128 > cus * 3 / 4 && 2 * t64 >= 5 * t128 && !single_bytes ? 128 : t64 > cus / 2 && t32 >= 2 * t64 ? 64 : 32;
+    if (element_wise_is_faster(g, tile, piece, tiles(tile), t64)) return CUBE3D_ENOTIMPL;
     if (tiles(tile) > MAX_WORKGROUPS) return CUBE3D_ENOTIMPL;
     p.tiles_m = (int)((g.Mo + tile - 1) / tile);
     p.tiles_n = (int)((g.No + tile - 1) / tile);

@@ -1,8 +1,9 @@
 // Shape-agnostic MFMA product kernel: every dtype, every operand layout, any
 // size (bounds-checked loads and stores, zero-filled tails, 64-bit addresses).  It is the
-// path for what the other two product kernels decline: operands that span 4 GB or more
-// (they address an operand by 32-bit offsets).  One workgroup (4 wavefronts) makes a 64x64
-// output tile; each wavefront owns one 32x32 MFMA accumulator.
+// path for what the other two product kernels decline: short contractions, where their
+// start-up counts (gemm_edge.hip says where), operands that span 4 GB or more (they address
+// an operand by 32-bit offsets), more tiles than one grid dimension holds.  One workgroup
+// (4 wavefronts) makes a 64x64 output tile; each wavefront owns one 32x32 MFMA accumulator.
 //
 // Implements the local products of Algorithm 1 step 3 and Algorithm 2 lines 1-2.
 #include "common.h"

@@ -39,3 +39,39 @@ def test_launches_stay_below_the_grid_limit(plans):
     assert plans([plain(c3.BF16, form, 1, 33600, 1, batch=64000) for form in LAYOUT]) == [(0, 0)] * 3
     for tile, piece in plans([plain(c3.BF16, form, 8, 64, 4096, batch=64000) for form in LAYOUT]):
         assert tile and -(-8 // tile) * -(-64 // tile) * 64000 < 1 << 24
+
+
+def cube(dtype, op, q, M, K, N, out=c3.BF16):
+    return "cube %d %d %d %d %d %d %d" % (dtype, out, op, q, M, K, N)
+
+
+# Short contractions: the element-wise kernel took 1.5 to 8 times less time than any tile on each of these.
+@pytest.mark.parametrize("line", [
+    plain(c3.BF16, c3.FORM_ABT, 1, 5, 9, 4096), plain(c3.FP8_E4M3, c3.FORM_ABT, 1, 4, 5, 4096),
+    plain(c3.BF16, c3.FORM_AB, 41, 41, 17, 4096), plain(c3.BF16, c3.FORM_AB, 40, 40, 16, 4096),
+    plain(c3.FP8_E4M3, c3.FORM_AB, 41, 41, 97, 4096), plain(c3.FP8_E4M3, c3.FORM_AB, 101, 201, 129, 512),
+    plain(c3.FP8_E4M3, c3.FORM_ABT, 8, 130, 66, 512), plain(c3.FP8_E4M3, c3.FORM_ATB, 3001, 3001, 257),
+    plain(c3.BF16, c3.FORM_AB, 3001, 3001, 33), plain(c3.F32, c3.FORM_AB, 3001, 3001, 17, out=c3.F32),
+    plain(c3.BF16, c3.FORM_AB, 1001, 1001, 17), plain(c3.F32, c3.FORM_AB, 41, 41, 17, 4096, out=c3.F32)])
+def test_short_contractions_run_element_by_element(plans, line):
+    assert plans([line]) == [(0, 0)]
+
+
+# Tiles that lie mostly beyond the output are not worth their time: 1.5 to 6 times as long with tiles of 128.
+@pytest.mark.parametrize("line,tile", [
+    (plain(c3.BF16, c3.FORM_AB, 41, 41, 1025, 4096), 64), (plain(c3.BF16, c3.FORM_AB, 9, 9, 1025, 4096), 32),
+    (plain(c3.BF16, c3.FORM_AB, 40, 40, 512, 4096), 64), (plain(c3.F32, c3.FORM_AB, 40, 40, 512, 4096, out=c3.F32), 64),
+    (plain(c3.FP8_E4M3, c3.FORM_ATB, 24, 24, 1024, 4096), 32), (plain(c3.BF16, c3.FORM_AB, 16, 256, 1024, 512), 64)])
+def test_small_blocks_run_on_small_tiles(plans, line, tile):
+    assert plans([line])[0][0] == tile
+
+
+# Longer contractions stay on the tiles.
+@pytest.mark.parametrize("line,want", [
+    (plain(c3.BF16, c3.FORM_AB, 3000, 3000, 64), (128, 16)), (plain(c3.BF16, c3.FORM_AB, 1000, 1000, 128), (64, 16)),
+    (plain(c3.F32, c3.FORM_AB, 128, 64, 64, 8, out=c3.F32), (32, 16)), (plain(c3.FP8_E4M3, c3.FORM_AB, 3001, 3001, 2049), (64, 1)),
+    (plain(c3.BF16, c3.FORM_ABT, 1001, 1001, 513), (64, 2)), (cube(c3.BF16, 0, 4, 64, 2048, 8192), (32, 16)),
+    (cube(c3.BF16, 2, 4, 64, 2048, 8192), (128, 16)), (cube(c3.FP8_E4M3, 1, 2, 3000, 3072, 12288), (128, 16)),
+    (cube(c3.BF16, 2, 3, 2997, 1152, 4608), (128, 16))])
+def test_longer_contractions_run_on_tiles(plans, line, want):
+    assert plans([line]) == [want]
