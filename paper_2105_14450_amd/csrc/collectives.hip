@@ -146,10 +146,8 @@ __device__ __forceinline__ RowMap map_copy_row(const CubeGeom &g, int mode, int 
 // VecT = what one lane moves per step; es = element size in bytes.  A wavefront works on the
 // four rows it owns in its block at the same time, four pieces per row in flight, so that every
 // lane has up to sixteen independent loads outstanding before the first store (the rows are
-// short: one row alone leaves the memory system idle).  Streaming stores: at 168 MB moved by
-// two scatters and two assembles 57.0 -> 53.9 us, at 470 MB 123 -> 113 us; the same time at 0.4-19 MB, where launches
-// count.
-template <typename VecT>
+// short: one row alone leaves the memory system idle).  STREAM: streaming stores, see copy_streams.
+template <typename VecT, bool STREAM>
 __global__ __launch_bounds__(256) void cube_copy_kernel(CubeGeom g, int mode, int64_t rows, int nseg, int es,
                                                         const char *__restrict__ src, char *__restrict__ dst)
 {
@@ -190,7 +188,10 @@ __global__ __launch_bounds__(256) void cube_copy_kernel(CubeGeom g, int mode, in
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int64_t c = c0 + 64 * u;
-                if (c < total && row0 + 4 * w < rows) __builtin_nontemporal_store(v[w][u], d[w] + c);
+                if (c < total && row0 + 4 * w < rows) {
+                    if (STREAM) __builtin_nontemporal_store(v[w][u], d[w] + c);
+                    else d[w][c] = v[w][u];
+                }
             }
     }
 }
@@ -405,6 +406,18 @@ int launch_reduce(const CubeGeom &g, int mode, int64_t rows, int64_t seg, const 
 
 }  // namespace
 
+// Whether a scatter or assemble of `bytes` writes with streaming stores: in pieces of 16 bytes, and when what it reads and writes
+// does not stay in the 256 MB Infinity Cache for the next call anyway.  us with plain / streaming stores, alone and
+// with an element-wise pass over the result behind it, 16-byte pieces: 192 MiB 87 / 72 and 159 / 158, 256 MiB 114 / 97
+// and 216 / 211, 512 MiB (scatter) 239 / 226 and 464 / 455.  Below, the next call pays for what the copy gains: 128 MiB 51 / 49 and 103 / 110,
+// 64 MiB 28 / 27 and 48 / 50; a scatter of 33 MB of weights before a product on 64 tokens 38 / 43.  Narrower pieces leave
+// cache lines in parts: 2 bytes, scatter and assemble of 64 MiB 123 / 157, of 512 MiB 1300 / 1450.
+static bool copy_streams(int64_t bytes)
+{
+    constexpr int64_t CACHE_BYTES = 256ll << 20;
+    return 2 * bytes > CACHE_BYTES;
+}
+
 // rows: destination rows per processor; nseg: source segments per destination row
 int cube_move(const CubeGeom &g, int mode, int es, const void *src, void *dst, hipStream_t stream)
 {
@@ -447,16 +460,18 @@ int cube_move(const CubeGeom &g, int mode, int es, const void *src, void *dst, h
     const int64_t nblk = (rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
     if (nblk > 0x7fffffff) return CUBE3D_ESHAPE;
     dim3 grid((unsigned)nblk, 1, (unsigned)(g.q * g.q * g.q));
+    const bool streams = copy_streams((int64_t)g.q * g.q * g.q * rows * nseg * seg_bytes);
     // every segment start is a multiple of the segment length, so alignment of the
     // segment length decides the widest safe vector
     if (seg_bytes % 16 == 0)
-        hipLaunchKernelGGL((cube_copy_kernel<i32x4>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
+        hipLaunchKernelGGL((streams ? cube_copy_kernel<i32x4, true> : cube_copy_kernel<i32x4, false>), grid, dim3(256), 0,
+                           stream, g, mode, rows, nseg, es, s, d);
     else if (seg_bytes % 4 == 0)
-        hipLaunchKernelGGL((cube_copy_kernel<int>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
+        hipLaunchKernelGGL((cube_copy_kernel<int, false>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
     else if (seg_bytes % 2 == 0)
-        hipLaunchKernelGGL((cube_copy_kernel<short>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
+        hipLaunchKernelGGL((cube_copy_kernel<short, false>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
     else
-        hipLaunchKernelGGL((cube_copy_kernel<char>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
+        hipLaunchKernelGGL((cube_copy_kernel<char, false>), grid, dim3(256), 0, stream, g, mode, rows, nseg, es, s, d);
     return launch_status();
 }
 
