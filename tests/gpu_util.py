@@ -87,3 +87,17 @@ def check_close(got: np.ndarray, ref: np.ndarray, kind: str, what: str):
 def workspace(desc, op, batched):
     n = c3.cube3d_workspace_bytes(desc, op, batched)
     return torch.empty(max(n, 16), dtype=torch.uint8, device="cuda") if n else None
+
+
+# Order of (i, a, b, rows of a shard, columns of a shard) in the full matrix, (row indices), (column indices), for a cube whose
+# input direction is y: X, W and Y / dY (Section 3.1.1).
+_SHARD_ORDER = {"x": ((0, 1, 3), (2, 4)), "w": ((2, 3), (1, 0, 4)), "y": ((0, 2, 3), (1, 4))}
+
+
+def device_shards(full: torch.Tensor, operand: str, q: int) -> torch.Tensor:
+    """Cube of shards [q^3, rows, columns] of a full matrix on the device, by index arithmetic only."""
+    rows, cols = _SHARD_ORDER[operand]
+    order = rows + cols
+    cut = [s for n, part in zip(full.shape, (rows, cols)) for s in [q] * (len(part) - 1) + [n // q ** (len(part) - 1)]]
+    t = full.reshape(cut).permute([order.index(d) for d in range(5)])
+    return t.reshape(q ** 3, *t.shape[3:]).contiguous()

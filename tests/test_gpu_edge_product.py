@@ -1,6 +1,7 @@
-"""Products of any size (GPU) against the oracle: edges of the 32 / 64 / 128 tiles, partial K-tiles, every width of a
-load piece, plain blocks and a cube of shards read in place.  Integers in [-4, 4]: all sums are exact, so every
-result is compared bit for bit."""
+"""Products of any size (GPU): edges of tiles and partial K-tiles on plain blocks and on a cube of shards read in place
+against the oracle, then every tile side, load width, operand layout and element type, the bits of calls with few and
+with many rows, operands at the limit of 32-bit offsets.  Integers in [-4, 4] wherever values are compared with a reference: all
+sums are exact, so every result is compared bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -12,6 +13,7 @@ from oracle.layout import Cube
 from paper_2105_14450_amd import synth
 
 import gpu_util as gu
+import product_shapes as ps
 
 pytestmark = pytest.mark.gpu
 
@@ -25,8 +27,8 @@ def _setup(q, M, K, N, dtype, out, seed):
     return inp, d, [numfmt.round_to(r, out) for r in ref]
 
 
-# pieces of 16 bytes (multiples of 16), 8 or 4 bytes, single elements; sizes below, at and above a tile and a K-tile;
-# many tiles of 128, some of 64, few of 32; contractions of one partial K-tile up to more than the pipeline's depth
+# loads of 16 bytes (multiples of 16), of 4, of single elements; sizes below, at and above a tile and a K-tile; mostly tiles
+# of 32 and 64, and element by element where the contraction is short
 @pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16")])
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (31, 16, 33), (33, 48, 80), (64, 656, 144), (65, 4, 130), (100, 130, 36),
                                    (127, 97, 129), (130, 336, 1040), (257, 1008, 272), (999, 24, 2064), (1700, 272, 2050)])
@@ -95,3 +97,97 @@ def test_very_many_thin_blocks():
     mm = c3.make_matmul(q, c3.FORM_AB, 1, n, 1, in_dtype=c3.BF16, out_dtype=c3.BF16)
     c3.cube3d_matmul_blocks(mm, a, b, c)
     assert torch.equal(c, b.mul_(a))            # products of integers up to 4: exact
+
+
+# ---- every kernel of the any-size product (which sizes reach which is asserted in test_product_dispatch.py) ----
+# Integers in [-4, 4] on the device; the reference is torch's fp32 product (exact: sums stay below 2^24), rounded once.
+
+CODES = {"f32": (torch.float32, c3.F32), "bf16": (torch.bfloat16, c3.BF16), "fp8_e4m3": (torch.float8_e4m3fn, c3.FP8_E4M3)}
+
+
+def _integers(shape, gen):
+    return torch.randint(-4, 5, shape, device="cuda", generator=gen, dtype=torch.int8).float()
+
+
+def _nan(shape, dtype):
+    return torch.full(shape, float("nan"), device="cuda", dtype=dtype)
+
+
+def _exactly(got, want, what):
+    assert torch.equal(got, want.to(got.dtype)), what
+
+
+@pytest.mark.parametrize("form", [c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB])
+@pytest.mark.parametrize("unit", sorted(ps.OUTPUTS))
+@pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16")])
+def test_every_tile_and_load_width(dtype, out, unit, form):
+    storage, code = CODES[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(unit)
+    for m, n in ps.OUTPUTS[unit]:
+        for k in ps.CONTRACTIONS[unit]:
+            a, b = _integers((m, k), gen), _integers((k, n), gen)
+            left = (a.t() if form == c3.FORM_ATB else a).contiguous().to(storage)
+            right = (b.t() if form == c3.FORM_ABT else b).contiguous().to(storage)
+            mm = c3.make_matmul(1, form, m, n, k, in_dtype=code, out_dtype=CODES[out][1])
+            got = _nan((m, n), CODES[out][0])
+            c3.cube3d_matmul_blocks(mm, left, right, got)
+            _exactly(got, a @ b, "%d x %d x %d" % (m, n, k))
+
+
+@pytest.mark.parametrize("unit", sorted(ps.CUBES))
+@pytest.mark.parametrize("dtype", ["bf16", "f32", "fp8_e4m3"])
+def test_every_tile_in_place_with_bias(dtype, unit):
+    q, (storage, code) = 3, CODES[dtype]
+    result = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(100 + unit)
+    for M, K, N in ps.CUBES[unit]:
+        X, W, G, bias = _integers((M, K), gen), _integers((K, N), gen), _integers((M, N), gen), _integers((N,), gen)
+        d = c3.make_desc(q, M, K, N, in_dtype=code, out_dtype=c3.F32, shard_dtype=CODES["f32" if dtype == "f32" else "bf16"][1])
+        x, w, g = (gu.device_shards(t, name, q).to(storage) for t, name in ((X, "x"), (W, "w"), (G, "y")))
+        diagonal = torch.zeros((q ** 3, N // q ** 2), device="cuda")
+        c3.virtual_cube_scatter(d, c3.OPERAND_BIAS, bias, diagonal)
+        y, dx, dw = _nan(g.shape, result), _nan(x.shape, result), _nan(w.shape, result)
+        c3.virtual_cube_linear_fwd(d, x, w, diagonal, y)
+        c3.virtual_cube_linear_bwd_dx(d, g, w, dx)
+        c3.virtual_cube_linear_bwd_dw(d, x, g, dw)
+        for got, want, name in ((y, X @ W + bias, "y"), (dx, G @ W.t(), "x"), (dw, X.t() @ G, "w")):
+            _exactly(got, gu.device_shards(want, name, q), "%s of %d x %d x %d" % (name, M, K, N))
+
+
+# An operand just below 4 GB is addressed by 32-bit offsets that nearly wrap; above, the element-wise kernel takes it.
+@pytest.mark.parametrize("above", [False, True])
+@pytest.mark.parametrize("dtype", sorted(ps.FOUR_GB))
+def test_operands_around_4_gb(dtype, above):
+    storage, code = CODES[dtype]
+    cols, n = ps.FOUR_GB[dtype][0], 16
+    rows = ps.FOUR_GB[dtype][2 if above else 1]
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    large = torch.randint(-4, 5, (rows, cols), device="cuda", generator=gen, dtype=torch.int8)
+    wide, tall = _integers((cols, n), gen), _integers((rows, n), gen)
+    stored, large = large.to(storage), large.float()
+    for form, right, shape, want in ((c3.FORM_AB, wide, (rows, n, cols), large @ wide),
+                                     (c3.FORM_ABT, wide.t().contiguous(), (rows, n, cols), large @ wide),
+                                     (c3.FORM_ATB, tall, (cols, n, rows), large.t() @ tall)):
+        mm = c3.make_matmul(1, form, *shape, in_dtype=code, out_dtype=c3.F32)
+        got = _nan(shape[:2], torch.float32)
+        c3.cube3d_matmul_blocks(mm, stored, right.to(storage), got)
+        _exactly(got, want, "form %d" % form)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_shards_above_4_gb_in_place(dtype):
+    q, (storage, code) = 2, CODES[dtype]
+    K, _, M = ps.FOUR_GB[dtype]
+    N = 16
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    X, W, G, bias = (_integers(s, gen) for s in ((M, K), (K, N), (M, N), (N,)))
+    d = c3.make_desc(q, M, K, N, in_dtype=code, out_dtype=c3.F32, shard_dtype=CODES[dtype][1])
+    x, w, g = (gu.device_shards(t, name, q).to(storage) for t, name in ((X, "x"), (W, "w"), (G, "y")))
+    diagonal = torch.zeros((q ** 3, N // q ** 2), device="cuda")
+    c3.virtual_cube_scatter(d, c3.OPERAND_BIAS, bias, diagonal)
+    y, dx, dw = (_nan(t.shape, storage) for t in (g, x, w))
+    c3.virtual_cube_linear_fwd(d, x, w, diagonal, y)
+    c3.virtual_cube_linear_bwd_dx(d, g, w, dx)
+    c3.virtual_cube_linear_bwd_dw(d, x, g, dw)
+    for got, want, name in ((y, X @ W + bias, "y"), (dx, G @ W.t(), "x"), (dw, X.t() @ G, "w")):
+        _exactly(got, gu.device_shards(want, name, q), name)

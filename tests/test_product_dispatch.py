@@ -8,6 +8,8 @@ import pytest
 import paper_2105_14450_amd as c3
 from paper_2105_14450_amd import build
 
+import product_shapes as ps
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LAYOUT = {c3.FORM_AB: (1, 0), c3.FORM_ABT: (1, 1), c3.FORM_ATB: (0, 0)}
 
@@ -75,3 +77,33 @@ def test_small_blocks_run_on_small_tiles(plans, line, tile):
     (cube(c3.BF16, 2, 3, 2997, 1152, 4608), (128, 16))])
 def test_longer_contractions_run_on_tiles(plans, line, want):
     assert plans([line]) == [want]
+
+
+def _kernel(dtype, tile, piece):
+    """The instantiation a plan runs on: (tile side, bytes per load)."""
+    return tile, 16 if piece >= 16 else 4 if piece >= 4 else {c3.F32: 4, c3.BF16: 2, c3.FP8_E4M3: 1}[dtype]
+
+
+# The sizes of the GPU tests reach all 69 kernels, those of a cube in place every one with tiles of 64 and 128.
+def test_gpu_tests_reach_every_kernel(plans):
+    widths = {c3.BF16: (16, 4, 2), c3.FP8_E4M3: (16, 4, 1), c3.F32: (16, 4)}
+    every = {(t, layout, tile, w) for t in widths for layout in LAYOUT.values() for tile in (32, 64, 128) for w in widths[t]
+             if not (w == 1 and tile == 128)}
+    assert len(every) == 69
+    asked = [(t, form, plain(t, form, m, n, k)) for t in widths for form in LAYOUT for u in ps.OUTPUTS
+             for m, n in ps.OUTPUTS[u] for k in ps.CONTRACTIONS[u]]
+    reached = {(t, LAYOUT[form], *_kernel(t, *plan)) for (t, form, _), plan in zip(asked, plans([a[2] for a in asked])) if plan[0]}
+    assert reached == every
+    asked = [(t, op, cube(t, op, 3, *sizes)) for t in widths for op in range(3) for u in ps.CUBES for sizes in ps.CUBES[u]]
+    layouts = tuple(LAYOUT[f] for f in (c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB))
+    reached = {(t, layouts[op], *_kernel(t, *plan)) for (t, op, _), plan in zip(asked, plans([a[2] for a in asked])) if plan[0]}
+    assert reached >= {x for x in every if x[2] > 32}, {x for x in every if x[2] > 32} - reached
+
+
+@pytest.mark.parametrize("name,dtype", [("f32", c3.F32), ("bf16", c3.BF16), ("fp8_e4m3", c3.FP8_E4M3)])
+def test_operands_of_4_gb_are_left_to_64_bit_addresses(plans, name, dtype):
+    cols, below, above = ps.FOUR_GB[name]
+    for rows, taken in ((below, True), (above, False)):
+        lines = [plain(dtype, c3.FORM_AB, rows, 16, cols), plain(dtype, c3.FORM_ABT, rows, 16, cols),
+                 plain(dtype, c3.FORM_ATB, cols, 16, rows), cube(dtype, 0, 2, rows, cols, 16), cube(dtype, 2, 2, rows, cols, 16)]
+        assert [plan[0] > 0 for plan in plans(lines)] == [taken] * 5
