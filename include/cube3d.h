@@ -285,7 +285,7 @@ int virtual_cube_bias_bwd(const cube3d_desc *desc, const void *dY_shards, void *
  * Any valid descriptor is accepted; shapes that fit the tuned kernel's tiles (bf16 or fp8 inputs,
  * M, K, N multiples of 128, the contraction length a multiple of four 64-byte K-tiles, shard
  * sizes multiples of 32, cube buffers shorter than 4 GB) run on it, the rest on the
- * bounds-checked kernel.
+ * kernels for any size.
  */
 int virtual_cube_linear_fwd(const cube3d_desc *desc, const void *X_shards, const void *W_shards, const void *bias_diag,
                             void *Y_shards, void *stream);

@@ -21,7 +21,15 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
 
 
 SCRATCH_LIMIT = 1024   # bytes per lane
+# The any-size kernels' K loops span several basic blocks, which the search below does not recognise as loops: no
+# scratch at all (none of them needs any).
+SCRATCH_LIMITS = {"gemm_edge_kernel": 0}
 MFMA_BLOCK = 8         # a basic block with at least this many MFMAs belongs to a K loop
+
+
+def scratch_limit(kernel):
+    """Bytes of scratch memory per lane that a kernel (mangled name) may use."""
+    return min([limit for part, limit in SCRATCH_LIMITS.items() if part in kernel], default=SCRATCH_LIMIT)
 
 
 def _spills_in_k_loops(asm_path):
@@ -68,7 +76,7 @@ def _compile(src):
             if "Function Name:" in line:
                 name = line.split("Function Name:")[1].split()[0]
             elif "ScratchSize" in line:
-                if int(line.split(":")[-1].split()[0]) > SCRATCH_LIMIT:
+                if int(line.split(":")[-1].split()[0]) > scratch_limit(name):
                     spilled.append(name)
             continue
         if "packed-fp32-ops" in line and "not a recognized feature" in line:

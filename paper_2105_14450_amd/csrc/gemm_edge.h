@@ -20,9 +20,11 @@
 // 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel that took these sizes before made 30-45 TFLOP/s.
 //
 // Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
-// stored), so only the last, partial K-tile looks at its bounds: it reads element 0 instead and writes zeros.
-// An operand is read in pieces of GB bytes: the widest power of two, up to 16, that divides every distance and
-// extent along the contiguous index, so no piece straddles a row, a shard or the buffer's end.
+// stored), so bounds are looked at along the contraction only: a piece beyond its end is read from element 0 and
+// written as zeros.  The prologue does that and the loop over the last D + 1 to 2 D + 1 K-tiles (D in flight);
+// the loop proper starts with more than 2 D whole K-tiles.  Both operands are read in pieces of GB bytes: 16, 4 or one element's, the widest
+// that divides every distance and extent along both contiguous indices, so no piece straddles a row, a shard or
+// the buffer's end.
 //
 // Address arithmetic.  Plain operands are a map with one endless panel.  From one K-tile to the next all of a
 // lane's byte offsets grow by one distance; only where a shard ends are they taken from the index map again (with
@@ -218,7 +220,6 @@ int make_plan(const GemmArgs &g, Plan *plan);
 
 template <int GB> struct Piece;
 template <> struct Piece<16> { typedef i32x4 Type; };
-template <> struct Piece<8> { typedef i32x2 Type; };
 template <> struct Piece<4> { typedef int Type; };
 template <> struct Piece<2> { typedef unsigned short Type; };
 template <> struct Piece<1> { typedef unsigned char Type; };
@@ -310,8 +311,9 @@ template <typename E, int T, int GB, bool KM> struct Operand {
     }
 };
 
-// K-tiles of loads in flight, in registers (T / 4 per lane and K-tile): as many as the accumulators leave
-// room for.  Pieces narrower than a register take one each: one K-tile.
+// K-tiles of loads in flight, in registers (T / 4 per lane and K-tile in pieces of 4 bytes and more, one per piece in
+// narrower ones): as many as the accumulators leave room for in pieces of 16 bytes.  Narrower pieces keep one K-tile, with an
+// offset register each; more was not tried for the 4-byte kernels, which use 60-70 registers at T = 32, 94-125 at T = 64.
 constexpr int depth(int T, int GB) { return GB < 16 ? 1 : T == 128 ? 2 : 4; }
 
 template <typename E, int T, int GB, bool AK, bool BK>

@@ -168,7 +168,7 @@ int launch_layout(const GemmArgs &g)
     } else if (g.a_kmajor && g.b_kmajor) CUBE3D_LAUNCH(true, true, false);
     else if (g.a_kmajor && !g.b_kmajor) CUBE3D_LAUNCH(true, false, false);
     else if (!g.a_kmajor && !g.b_kmajor) CUBE3D_LAUNCH(false, false, false);
-    else CUBE3D_LAUNCH(false, true, false);
+    else return CUBE3D_ENOTIMPL;
 #undef CUBE3D_LAUNCH
     return launch_status();
 }

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256, (BM * BN <= 128 * 128) ? 2 : 1) void gemm_mfma
     constexpr int NBUF = MAPPED ? 1 : 2;
     // The optional bias belongs to the forward product (Algorithm 7 follows Algorithm 1): only the
     // map-addressed kernel of that layout stages and adds it; the launcher sends a bias with any other
-    // layout to the bounds-checked kernel.
+    // layout to the kernels for any size.
     constexpr bool BIAS = MAPPED && AK && !BKM;
     constexpr int STRIP_BYTES = 32 * ROWB;
     constexpr int EPI_BYTES = NBUF * STRIP_BYTES;

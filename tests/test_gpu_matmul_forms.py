@@ -105,7 +105,7 @@ CASES = [
     (2, "AB", 256, 128, 128, "f32", "f32", "f32"),
     (2, "ABT", 256, 128, 128, "f32", "f32", "f32"),
     (2, "ATB", 256, 128, 128, "f32", "f32", "f32"),
-    (3, "ABT", 72, 36, 54, "f32", "f32", "f32"),                  # ragged: bounds-checked kernels
+    (3, "ABT", 72, 36, 54, "f32", "f32", "f32"),                  # ragged: the kernels for any size
     (3, "ATB", 36, 72, 45, "bf16", "f32", "bf16"),
     (2, "ABT", 512, 512, 1024, "bf16", "f32", "bf16"),            # tuned kernel, 256-wide blocks
     (2, "ATB", 512, 512, 1024, "bf16", "bf16", "bf16"),

@@ -165,7 +165,7 @@ CASES = [
     # q, M, K, N1, N2, dtype, dist, kind
     (2, 256, 128, 512, 128, "f32", "int", "relu"),          # exact end to end
     (2, 256, 128, 512, 128, "f32", "uniform", "gelu"),
-    (3, 180, 63, 117, 45, "bf16", "normal", "gelu"),        # ragged: bounds-checked kernels
+    (3, 180, 63, 117, 45, "bf16", "normal", "gelu"),        # ragged: the kernels for any size
     (2, 512, 256, 1024, 256, "bf16", "int", "relu"),        # tuned kernels (small tiles)
     (2, 1024, 512, 2048, 512, "bf16", "normal", "gelu"),    # tuned kernels, hidden -> 4 x hidden -> hidden
 ]
