@@ -16,7 +16,7 @@
 // per-lane walk 26 (33 MB of weights: 5 us at 7 TB/s).  32 x 32 tiles whose wavefronts shared the k-steps, as in
 // fp32, took 22 there and 23 against 26 for 64 x 2048 x 8192 with W^T, but 7.2 against 6.7 for 64 x 512 x 512, and their four
 // partial sums made a row's bits depend on how many rows the call had.  With many workgroups LDS reads and vector instructions share
-// the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 237 us = 0.76 PFLOP/s, three fp8 products of
+// the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 234-252 us = 0.71-0.77 PFLOP/s, three fp8 products of
 // 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel that took these sizes before made 30-45 TFLOP/s.
 //
 // Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
