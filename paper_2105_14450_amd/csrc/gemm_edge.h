@@ -13,7 +13,7 @@
 // What bounds it.  With few workgroups per CU the chain of one K-tile: 64 rows x 8192 x 2048 bf16 took 63 us on 32
 // tiles of 64 with one K-tile of loads in flight; four in flight, waits that count exactly one K-tile's loads and
 // fragment reads ahead of the LDS writes made it 40, the 32 x 32 tiles and one vector addition per load in place of a
-// per-lane walk 26 (33 MB of weights: 5 us at 7 TB/s).  32 x 32 tiles whose wavefronts shared the k-steps, as in
+// per-lane walk 24 (33 MB of weights: 5 us at 7 TB/s).  32 x 32 tiles whose wavefronts shared the k-steps, as in
 // fp32, took 22 there and 23 against 26 for 64 x 2048 x 8192 with W^T, but 7.2 against 6.7 for 64 x 512 x 512, and their four
 // partial sums made a row's bits depend on how many rows the call had.  With many workgroups LDS reads and vector instructions share
 // the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 234-252 us = 0.71-0.77 PFLOP/s, three fp8 products of
@@ -48,10 +48,10 @@ constexpr int BKB = 128;      // bytes of contraction index per K-tile and row
 // accumulator, and M16 gives the bits of M32 (compared on random operands over 512 indices): a row of the
 // result does not depend on the tile side, that is on how many other rows the call has.
 //   mn_swz: slot permutation of an MN-major row (spr 16-byte slots) in k-row k, so that the k-rows that one
-//   read covers lie in different banks
+//   read covers lie in different banks (32 x 32 tiles: 26.2 -> 24.4 us for 64 x 8192 x 2048)
 struct Bf16 {
     static constexpr int ELT = 2;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 0; }
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 2 * ((k >> 3) & 1); }
     struct M32 {
         static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;      // MFMAS: MFMAs per fragment pair
         typedef i32x4 Frag;
@@ -105,7 +105,7 @@ struct Bf16 {
 
 struct Fp8 {
     static constexpr int ELT = 1;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : 0; }
+    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : (k >> 3) & 1; }
     struct M32 {
         static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;
         typedef i32x2 Frag;
@@ -263,7 +263,7 @@ template <typename E, int T, int GB, bool KM> struct Operand {
         base = b;
         const int row = tid / SPR, slot = tid % SPR;
         // (a lane's rows are PASS apart: a multiple of what the permutations depend on)
-        static_assert(PASS % (KM ? 16 : 8) == 0, "the permutation is the same for a lane's slots");
+        static_assert(PASS % (KM || T == 32 ? 16 : 8) == 0, "the permutation is the same for a lane's slots");
         lds = row * RB + ((slot ^ (KM ? (row / 2) % 8 : E::mn_swz(row, SPR))) * 16);
         kfirst = KM ? slot * EPS : row;
 #pragma unroll

@@ -140,8 +140,8 @@ int make_plan(const GemmArgs &g, Plan *plan)
     // Tile side: the largest that still gives most CUs a tile, because a CU without one costs more than the
     // smaller tile's extra LDS reads.  bf16, us with 128 / 64 / 32 at (Mo, No, Kc): (2997, 1152, 4608) with B K-major = 216 tiles
     // of 128: 52 / 66 / 93; (3000, 1024, 4096) = 192: 46 / 47 / 70; (1000, 2048, 1024) = 128, fp8: 15 / 11 / 14;
-    // (384, 1536, 999) with no operand K-major = 144 tiles of 64: 18 / 10.7 / 12.7; (64, 8192, 2048) = 128: 27 / 15.6 / 15.4;
-    // (999, 384, 1536) = 96: 22 / 12.7 / 11.2; (64, 2048, 8192) = 32: 84 / 40 / 26.  The other types and widths cross at the
+    // (384, 1536, 999) with no operand K-major = 144 tiles of 64: 18 / 10.7 / 12.7; (64, 8192, 2048) = 128: 27 / 15.7 / 15.3;
+    // (999, 384, 1536) = 96: 22 / 12.7 / 10.8; (64, 2048, 8192) = 32: 84 / 40 / 24.  The other types and widths cross at the
     // same places: fp32 (1004, 1004, 1028) = 256 tiles of 64: 78 / 33 / 34, (404, 404, 1028) = 49: 76 / 29 / 14; bf16 read
     // singly (3001, 3001, 1025) = 576 of 128: 182 / 207 / 532, (1001, 1001, 1025) = 256 of 64: 67 / 30 / 60, (401, 401, 1025) = 49: 67 / 30 / 20;
     // but fp32 (3004, 3004, 1028), whose 576 tiles of 128 take two rounds where one and an eighth would do: 213 / 187 / 216.
