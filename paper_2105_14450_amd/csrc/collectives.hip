@@ -406,12 +406,13 @@ int launch_reduce(const CubeGeom &g, int mode, int64_t rows, int64_t seg, const 
 
 }  // namespace
 
-// Whether a scatter or assemble of `bytes` writes with streaming stores: in pieces of 16 bytes, and when what it reads and writes
-// does not stay in the 256 MB Infinity Cache for the next call anyway.  us with plain / streaming stores, alone and
-// with an element-wise pass over the result behind it, 16-byte pieces: 192 MiB 87 / 72 and 159 / 158, 256 MiB 114 / 97
-// and 216 / 211, 512 MiB (scatter) 239 / 226 and 464 / 455.  Below, the next call pays for what the copy gains: 128 MiB 51 / 49 and 103 / 110,
-// 64 MiB 28 / 27 and 48 / 50; a scatter of 33 MB of weights before a product on 64 tokens 38 / 43.  Narrower pieces leave
-// cache lines in parts: 2 bytes, scatter and assemble of 64 MiB 123 / 157, of 512 MiB 1300 / 1450.
+// Whether a scatter or assemble of `bytes` in 16-byte pieces writes with streaming stores: when what it reads and
+// writes does not stay in the 256 MB Infinity Cache for the next call anyway.  us with plain / streaming stores, alone
+// and with an element-wise pass over the result behind it: 192 MiB 87 / 72 and 159 / 158, 256 MiB 114 / 97 and
+// 216 / 211, 512 MiB (scatter) 239 / 226 and 464 / 455.  Below, the next call pays for what the copy gains: 128 MiB
+// 51 / 49 and 103 / 110, 64 MiB 28 / 27 and 48 / 50; a scatter of 33 MB of weights and a product on 64 tokens 38 / 43.
+// Narrower pieces never: they leave a cache line in parts (2 bytes, scatter and assemble of 64 MiB 123 / 157, of
+// 512 MiB 1300 / 1450).
 static bool copy_streams(int64_t bytes)
 {
     constexpr int64_t CACHE_BYTES = 256ll << 20;

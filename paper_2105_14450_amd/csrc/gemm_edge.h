@@ -14,17 +14,18 @@
 // tiles of 64 with one K-tile of loads in flight; four in flight, waits that count exactly one K-tile's loads and
 // fragment reads ahead of the LDS writes made it 40, the 32 x 32 tiles and one vector addition per load in place of a
 // per-lane walk 24 (33 MB of weights: 5 us at 7 TB/s).  32 x 32 tiles whose wavefronts shared the k-steps, as in
-// fp32, took 22 there and 23 against 26 for 64 x 2048 x 8192 with W^T, but 7.2 against 6.7 for 64 x 512 x 512, and their four
-// partial sums made a row's bits depend on how many rows the call had.  With many workgroups LDS reads and vector instructions share
-// the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 234-252 us = 0.71-0.77 PFLOP/s, three fp8 products of
-// 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel that took these sizes before made 30-45 TFLOP/s.
+// fp32, took 22 there and 23 against 26 for 64 x 2048 x 8192 with W^T, but 7.2 against 6.7 for 64 x 512 x 512, and
+// their four partial sums made a row's bits depend on how many rows the call had.  With many workgroups LDS reads
+// and vector instructions share the time with the MFMAs: 6000 x 3000 x 5000 bf16 takes 232-252 us = 0.71-0.78
+// PFLOP/s, three fp8 products of 3000 x 3072 x 12288 590 us = 1.15 PFLOP/s; the element-wise kernel makes 30-45
+// TFLOP/s at these sizes.
 //
 // Edges.  Rows and columns beyond the output are read from the last valid one (their sums are never
 // stored), so bounds are looked at along the contraction only: a piece beyond its end is read from element 0 and
 // written as zeros.  The prologue does that and the loop over the last D + 1 to 2 D + 1 K-tiles (D in flight);
-// the loop proper starts with more than 2 D whole K-tiles.  Both operands are read in pieces of GB bytes: 16, 4 or one element's, the widest
-// that divides every distance and extent along both contiguous indices, so no piece straddles a row, a shard or
-// the buffer's end.
+// the loop proper starts with more than 2 D whole K-tiles.  Both operands are read in pieces of GB bytes: 16, 4 or
+// one element's, the widest that divides every distance and extent along both contiguous indices, so no piece
+// straddles a row, a shard or the buffer's end.
 //
 // Address arithmetic.  Plain operands are a map with one endless panel.  From one K-tile to the next all of a
 // lane's byte offsets grow by one distance; only where a shard ends are they taken from the index map again (with
@@ -51,7 +52,10 @@ constexpr int BKB = 128;      // bytes of contraction index per K-tile and row
 //   read covers lie in different banks (32 x 32 tiles: 26.2 -> 24.4 us for 64 x 8192 x 2048)
 struct Bf16 {
     static constexpr int ELT = 2;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 2 * ((k >> 3) & 1); }
+    __device__ static __forceinline__ int mn_swz(int k, int spr)
+    {
+        return spr >= 16 ? 4 * (k & 3) : spr >= 8 ? 4 * ((k >> 1) & 1) : 2 * ((k >> 3) & 1);
+    }
     struct M32 {
         static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;      // MFMAS: MFMAs per fragment pair
         typedef i32x4 Frag;
@@ -105,7 +109,10 @@ struct Bf16 {
 
 struct Fp8 {
     static constexpr int ELT = 1;
-    __device__ static __forceinline__ int mn_swz(int k, int spr) { return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : (k >> 3) & 1; }
+    __device__ static __forceinline__ int mn_swz(int k, int spr)
+    {
+        return spr >= 8 ? 2 * ((k >> 1) & 3) : spr >= 4 ? 2 * ((k >> 2) & 1) : (k >> 3) & 1;
+    }
     struct M32 {
         static constexpr int SIDE = 32, KSTEP = 16, MFMAS = 1;
         typedef i32x2 Frag;
@@ -325,7 +332,8 @@ __global__ __launch_bounds__(256, T == 128 || GB == 1 ? 2 : 3) void gemm_edge_ke
     typedef typename M::Frag Frag;
     typedef typename M::Acc Acc;
     constexpr int SIDE = M::SIDE, VALS = SIDE * SIDE / 64;      // an accumulator block and a lane's values of it
-    constexpr int TK = OA::TK, STEPS = TK / M::KSTEP, KW = Instr<E, T>::KW, W = KW == 1 ? T / 2 : T, NB = W / SIDE, D = depth(T, GB);
+    constexpr int KW = Instr<E, T>::KW, W = KW == 1 ? T / 2 : T, NB = W / SIDE;
+    constexpr int TK = OA::TK, STEPS = TK / M::KSTEP, D = depth(T, GB);
     constexpr int STAGE = OA::BYTES + OB::BYTES;
     constexpr int STRIP = W * 4 + 16;                   // bytes of a staged output row (fp32, padded)
     constexpr int LDS = 2 * STAGE > 4 * SIDE * STRIP ? 2 * STAGE : 4 * SIDE * STRIP;   // the strips reuse the K-tile buffers

@@ -39,11 +39,12 @@ int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t bat
     return piece;
 }
 
-// Estimated time of a launch in us, to compare this kernel with the element-wise one (gemm_generic) where the contraction is
-// short: a workgroup here pays for its pipeline's start and its staged output however few K-tiles it has, an element-wise
-// one next to nothing besides its steps of 32.  Fitted to 1700 products of 1-4096 blocks with a contraction of 1-640
-// on one MI355X, all kernels timed at each; over 2450 products the choice is 1.2 % slower than the best one in the
-// mean, and at 55 of them more than 5 % slower than the element-wise kernel (at most 1.46 times; without it at 1120, up to 8 times).
+// Estimated time of a launch in us, to compare this kernel with the element-wise one (gemm_generic) where the
+// contraction is short: a workgroup here pays for its pipeline's start and its staged output however few K-tiles it
+// has, an element-wise one next to nothing besides its steps of 32.  Fitted to 1700 products of 1-4096 blocks with a
+// contraction of 1-700 on one MI355X, all kernels timed at each.  Over 2450 products the choice is 1.2 % slower than
+// the best one in the mean, and at 55 of them more than 5 % slower than the element-wise kernel (at most 1.46 times;
+// with the tile rule alone at 1120, up to 8 times).
 //   start: launch, first loads, output;  tile, ktile: per workgroup and per K-tile of it when all CUs are busy
 struct Cost {
     float start, tile, ktile;
@@ -66,13 +67,15 @@ struct ElementCost {
 };
 constexpr ElementCost ELEMENT_COST[3] = {{4.79f, 2.44f, 0.43f, 0.53f}, {4.82f, 2.56f, 0.41f, 0.44f}, {4.74f, 1.69f, 0.85f, 0.68f}};
 constexpr float ELEMENT_MAPS = 3.f;      // an index map divides four times per element: 2.4-3.2 times a step's time
-constexpr int64_t SHORT = 640;           // beyond, its steps leave the caches and the fit; bytes read singly (fp8) cross at about
-                                         // 1000-2000: 3001 x 3001 x 1025, 286 here against 253 us
+// Beyond, its steps leave the caches and the fit.  (fp8 read in single bytes crosses at about 1000-2000: 3001 x 3001 x 1025
+// 286 here against 253 us, 4096 blocks of 41 x 41 x 1025 376-397 against 433-507.)
+constexpr int64_t SHORT = 640;
 
 bool element_wise_is_faster(const GemmArgs &g, int tile, int piece, int64_t workgroups, int64_t workgroups64)
 {
     if (g.Kc > SHORT) return false;
-    const int type = g.in_dtype == CUBE3D_BF16 ? 0 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 2, es = type == 0 ? 2 : type == 1 ? 1 : 4;
+    const int type = g.in_dtype == CUBE3D_BF16 ? 0 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 2;
+    const int es = type == 0 ? 2 : type == 1 ? 1 : 4;
     const Cost &c = COST[3 * type + (piece >= 16 ? 0 : piece >= 4 ? 1 : 2)][tile == 32 ? 0 : tile == 64 ? 1 : 2];
     const ElementCost &e = ELEMENT_COST[type];
     const float cus = (float)num_compute_units(), per_cu = (float)workgroups / cus, per_cu64 = (float)workgroups64 / cus;
@@ -142,15 +145,16 @@ int make_plan(const GemmArgs &g, Plan *plan)
     // of 128: 52 / 66 / 93; (3000, 1024, 4096) = 192: 46 / 47 / 70; (1000, 2048, 1024) = 128, fp8: 15 / 11 / 14;
     // (384, 1536, 999) with no operand K-major = 144 tiles of 64: 18 / 10.7 / 12.7; (64, 8192, 2048) = 128: 27 / 15.7 / 15.3;
     // (999, 384, 1536) = 96: 22 / 12.7 / 10.8; (64, 2048, 8192) = 32: 84 / 40 / 24.  The other types and widths cross at the
-    // same places: fp32 (1004, 1004, 1028) = 256 tiles of 64: 78 / 33 / 34, (404, 404, 1028) = 49: 76 / 29 / 14; bf16 read
-    // singly (3001, 3001, 1025) = 576 of 128: 182 / 207 / 532, (1001, 1001, 1025) = 256 of 64: 67 / 30 / 60, (401, 401, 1025) = 49: 67 / 30 / 20;
-    // but fp32 (3004, 3004, 1028), whose 576 tiles of 128 take two rounds where one and an eighth would do: 213 / 187 / 216.
+    // same places: fp32 (1004, 1004, 1028) = 256 tiles of 64: 78 / 33 / 34, (404, 404, 1028) = 49: 76 / 29 / 14; bf16 in
+    // single elements (3001, 3001, 1025) = 576 of 128: 182 / 207 / 532, (1001, 1001, 1025) = 256 of 64: 67 / 30 / 60,
+    // (401, 401, 1025) = 49: 67 / 30 / 20.  Not so fp32 (3004, 3004, 1028), 576 tiles of 128 for 512 places: 213 / 187 / 216.
     // And not where most of the larger tile lies beyond the output: it takes the time of two to three half as wide.
     // 4096 blocks, bf16: 41 x 41 x 1025 684 / 370 / 662, 41 x 41 x 129 151 / 70 / 130, 9 x 9 x 1025 481 / 222 / 120,
     // 24 x 104 x 1032 224 / 250 / 304; 512 of 101 x 201 x 257 82 / 122 / 220; fp8, 304 x 528 x 144 121 / 162 / 253.
     const int64_t cus = num_compute_units(), t32 = tiles(32), t64 = tiles(64), t128 = tiles(128);
     const bool single_bytes = piece < 4 && es == 1;      // no 128 x 128 kernel, see launch_tile
-    const int tile = plan->tile = t128 > cus * 3 / 4 && 2 * t64 >= 5 * t128 && !single_bytes ? 128 : t64 > cus / 2 && t32 >= 2 * t64 ? 64 : 32;
+    const bool large = t128 > cus * 3 / 4 && 2 * t64 >= 5 * t128 && !single_bytes, medium = t64 > cus / 2 && t32 >= 2 * t64;
+    const int tile = plan->tile = large ? 128 : medium ? 64 : 32;
     if (element_wise_is_faster(g, tile, piece, tiles(tile), t64)) return CUBE3D_ENOTIMPL;
     if (tiles(tile) > MAX_WORKGROUPS) return CUBE3D_ENOTIMPL;
     p.tiles_m = (int)((g.Mo + tile - 1) / tile);
