@@ -41,48 +41,59 @@ int64_t piece_of(const AxisMap &c, const AxisMap &r, int64_t extent, int64_t bat
 
 // Estimated time of a launch in us, to compare this kernel with the element-wise one (gemm_generic) where the
 // contraction is short: a workgroup here pays for its pipeline's start and its staged output however few K-tiles it
-// has, an element-wise one next to nothing besides its steps of 32.  Fitted to 1700 products of 1-4096 blocks with a
-// contraction of 1-700 on one MI355X, all kernels timed at each.  Over 2450 products the choice is 1.2 % slower than
-// the best one in the mean, and at 55 of them more than 5 % slower than the element-wise kernel (at most 1.46 times;
-// with the tile rule alone at 1120, up to 8 times).
-//   start: launch, first loads, output;  tile, ktile: per workgroup and per K-tile of it when all CUs are busy
+// has, an element-wise one next to nothing besides its steps of 32.  Fitted to products of 1-4096 blocks on one
+// MI355X, all kernels timed at each.  Over 3130 products the choice is 1.1 % slower than the best one in the mean, and at
+// 56 of them more than 5 % slower than the element-wise kernel (at most 1.44 times; with the tile rule alone at 1400,
+// up to 8 times).
+//   start: launch, first loads, output;  tile, ktile, full: per workgroup, per K-tile of it, and more per K-tile the fuller
+//   the tiles are, when all CUs are busy
 struct Cost {
-    float start, tile, ktile;
+    float start, tile, ktile, full;
 };
 constexpr Cost COST[8][3] = {
-    // tiles of 32                64                    128
-    {{5.25f, 0.47f, 0.06f}, {5.68f, 1.15f, 0.28f}, {9.66f, 2.12f, 0.76f}},      // bf16, loads of 16 bytes
-    {{6.10f, 0.57f, 0.19f}, {8.03f, 0.90f, 0.55f}, {17.0f, 4.08f, 1.35f}},      //       4
-    {{6.77f, 0.67f, 0.41f}, {9.13f, 1.11f, 1.03f}, {19.0f, 3.40f, 2.88f}},      //       2
-    {{5.29f, 0.50f, 0.05f}, {5.47f, 1.23f, 0.25f}, {9.69f, 2.19f, 0.84f}},      // fp8, loads of 16 bytes
-    {{6.03f, 0.63f, 0.16f}, {7.82f, 1.03f, 0.48f}, {13.1f, 4.15f, 1.48f}},      //      4
-    {{7.59f, 0.94f, 1.04f}, {8.92f, 2.79f, 2.38f}, {8.92f, 2.79f, 2.38f}},      //      1 (no tiles of 128)
-    {{5.44f, 0.84f, 0.18f}, {6.56f, 1.26f, 0.65f}, {11.6f, 3.54f, 2.17f}},      // fp32, loads of 16 bytes
-    {{5.83f, 0.84f, 0.24f}, {8.74f, 1.09f, 0.78f}, {17.4f, 5.00f, 2.69f}},      //       4
+    // tiles of 32                       64                                  128
+    {{5.14f, 0.48f, 0.05f, 0.09f}, {5.46f, 1.14f, 0.24f, 0.19f}, {7.30f, 2.48f, 0.00f, 1.01f}},    // bf16, loads of 16 bytes
+    {{5.79f, 0.62f, 0.13f, 0.28f}, {7.56f, 0.96f, 0.39f, 0.39f}, {8.90f, 4.92f, 0.00f, 2.17f}},    //       4
+    {{6.02f, 0.84f, 0.27f, 0.60f}, {7.88f, 1.35f, 0.65f, 0.93f}, {12.4f, 3.97f, 0.28f, 3.93f}},    //       2
+    {{5.21f, 0.49f, 0.04f, 0.10f}, {5.46f, 1.25f, 0.00f, 0.41f}, {6.87f, 2.42f, 0.00f, 1.34f}},    // fp8, loads of 16 bytes
+    {{5.86f, 0.63f, 0.13f, 0.18f}, {7.27f, 1.08f, 0.16f, 0.88f}, {10.2f, 4.56f, 0.00f, 2.37f}},    //      4
+    {{6.61f, 1.28f, 0.76f, 0.97f}, {8.12f, 2.67f, 1.52f, 1.89f}, {}},                              //      1 (no tiles of 128)
+    {{5.32f, 0.85f, 0.17f, 0.07f}, {6.02f, 1.32f, 0.53f, 0.31f}, {7.87f, 3.79f, 0.85f, 1.88f}},    // fp32, loads of 16 bytes
+    {{5.38f, 0.90f, 0.20f, 0.22f}, {7.61f, 1.18f, 0.56f, 0.60f}, {12.4f, 5.25f, 0.73f, 2.83f}},    //       4
 };
-//   least: workgroups per CU below which a launch gets no faster;  step, full: per step of 32, and more of it the fuller
-//   the tiles are (elements beyond the edges are not loaded)
+//   step, full: per workgroup and step of 32, and more of it the fuller the tiles are (elements beyond the edges are not loaded)
+//   least: workgroups per CU below which a step gets no faster, for one block or about one workgroup per CU;  several:
+//   for more blocks, which share less through the caches;  one: what a step of one block's workgroups takes of that
 struct ElementCost {
-    float start, least, step, full;
+    float start, least, several, step, full, one;
 };
-constexpr ElementCost ELEMENT_COST[3] = {{4.79f, 2.44f, 0.43f, 0.53f}, {4.82f, 2.56f, 0.41f, 0.44f}, {4.74f, 1.69f, 0.85f, 0.68f}};
+constexpr ElementCost ELEMENT_COST[3] = {{4.73f, 2.26f, 3.47f, 0.40f, 0.64f, 0.94f},      // bf16
+                                         {4.65f, 2.41f, 3.64f, 0.38f, 0.53f, 0.91f},      // fp8
+                                         {4.34f, 1.70f, 3.23f, 0.80f, 0.84f, 0.90f}};     // fp32
 constexpr float ELEMENT_MAPS = 3.f;      // an index map divides four times per element: 2.4-3.2 times a step's time
-// Beyond, its steps leave the caches and the fit.  (fp8 read in single bytes crosses at about 1000-2000: 3001 x 3001 x 1025
-// 286 here against 253 us, 4096 blocks of 41 x 41 x 1025 376-397 against 433-507.)
-constexpr int64_t SHORT = 640;
+// Beyond, its steps leave the caches and the fit: sooner with several blocks on few workgroups per CU (8 of 407 x 521 x 799
+// fp8 in single bytes 60 here against 121 us), later with single bytes and mostly full tiles (3001 x 3001 x 1025 286
+// against 253, x 2049 523 against 506; but 4096 blocks of 41 x 41 x 1025 397 against 433).
+constexpr int64_t SHORT_FEW = 384, SHORT = 640, SHORT_SINGLE_BYTES = 2048;
 
 bool element_wise_is_faster(const GemmArgs &g, int tile, int piece, int64_t workgroups, int64_t workgroups64)
 {
-    if (g.Kc > SHORT) return false;
     const int type = g.in_dtype == CUBE3D_BF16 ? 0 : g.in_dtype == CUBE3D_FP8_E4M3 ? 1 : 2;
-    const int es = type == 0 ? 2 : type == 1 ? 1 : 4;
-    const Cost &c = COST[3 * type + (piece >= 16 ? 0 : piece >= 4 ? 1 : 2)][tile == 32 ? 0 : tile == 64 ? 1 : 2];
-    const ElementCost &e = ELEMENT_COST[type];
+    const int es = type == 0 ? 2 : type == 1 ? 1 : 4, width = piece >= 16 ? 0 : piece >= 4 ? 1 : 2;
+    const double elements = (double)g.Mo * (double)g.No * g.batch;
     const float cus = (float)num_compute_units(), per_cu = (float)workgroups / cus, per_cu64 = (float)workgroups64 / cus;
-    const float full = (float)((double)g.Mo * (double)g.No * g.batch / ((double)workgroups64 * 64 * 64));
-    const float here = c.start + (per_cu > 1.f ? per_cu : 1.f) * (c.tile + c.ktile * (float)((g.Kc * es + BKB - 1) / BKB));
+    const float full = (float)(elements / ((double)workgroups * tile * tile));
+    const float full64 = (float)(elements / ((double)workgroups64 * 64 * 64));
+    const bool one = g.batch == 1, single_bytes = es == 1 && width == 2;
+    const int64_t limit = !one && per_cu64 < 6.f ? SHORT_FEW : single_bytes && full64 >= 0.5f ? SHORT_SINGLE_BYTES : SHORT;
+    if (g.Kc > limit) return false;
+    const Cost &c = COST[3 * type + width][tile == 32 ? 0 : tile == 64 ? 1 : 2];
+    const float ktiles = (float)((g.Kc * es + BKB - 1) / BKB);
+    const float here = c.start + (per_cu > 1.f ? per_cu : 1.f) * (c.tile + (c.ktile + c.full * full) * ktiles);
+    const ElementCost &e = ELEMENT_COST[type];
+    const float least = one || per_cu64 <= 1.3f ? e.least : e.several, busy = one ? e.one * per_cu64 : per_cu64;
     const float steps = (float)((g.Kc + 31) / 32) * (g.maps ? ELEMENT_MAPS : 1.f);
-    return e.start + (per_cu64 > e.least ? per_cu64 : e.least) * steps * (e.step + e.full * full) < here;
+    return e.start + steps * (busy > least ? busy : least) * (e.step + e.full * full64) < here;
 }
 
 // A launch has fewer than 2^32 work-items along a grid dimension: 2^24 workgroups of 256.
