@@ -53,10 +53,12 @@ inline void prepare_axis_map(AxisMap &m)
         int L = 0;
         while ((1ll << L) < P) ++L;
         *N = 31 + L;
-        *M = (uint64_t)(((((unsigned __int128)1) << *N) + (unsigned)P - 1) / (unsigned)P);
+        *M = ((1ull << *N) + (unsigned)P - 1) / (unsigned)P;      // N <= 62
     };
     magic(m.P1, &m.M1, &m.N1);
-    magic(m.P2, &m.M2, &m.N2);
+    m.M2 = m.M1;
+    m.N2 = m.N1;
+    if (m.P2 != m.P1) magic(m.P2, &m.M2, &m.N2);
 }
 
 __host__ __device__ __forceinline__ int64_t axis_offset(const AxisMap &m, int64_t x)
@@ -118,6 +120,8 @@ int gemm_generic(const GemmArgs &g);
 // Any size and dtype; CUBE3D_ENOTIMPL where gemm_generic is faster (short contractions) or has to take it: operands that
 // span 4 GB or more, 2^24 tiles or more; also what gemm_generic refuses (more than 64 * 65535 rows, 65535 blocks).
 int gemm_edge(const GemmArgs &g);
+// Estimated time in us where its ring kernel takes the product, else infinity.
+float gemm_edge_estimate(const GemmArgs &g);
 
 // Tuned bf16 / fp8 path; returns CUBE3D_ENOTIMPL when the shape does not fit its tiles.
 int gemm_fast(const GemmArgs &g);

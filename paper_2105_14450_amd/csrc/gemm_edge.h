@@ -1,7 +1,8 @@
 // Product kernel without size classes, for gfx950: any Mo, No and Kc, fp32 / bf16 / fp8-e4m3 operands, plain
 // leading dimensions or a cube of shards read in place.  It takes what the tile-aligned kernel
 // (gemm_mfma_kernel.h) declines: ragged sizes, few rows, fp32.  The local products of Algorithm 1 step 3 and
-// Algorithm 2 lines 1-2.
+// Algorithm 2 lines 1-2.  Operands that can be read in 16-byte pieces mostly go to the ring kernel instead
+// (gemm_ring.h; ring_plan says which); the figures below are this kernel's.
 //
 // Work split.  A workgroup of four wavefronts makes a T x T tile: T = 128 or 64 as 2 x 2 sub-tiles in 32x32
 // MFMA accumulators, T = 32 as 2 x 2 blocks of 16x16 MFMAs (bf16, fp8) or as one block whose k-steps the wavefronts
@@ -205,6 +206,12 @@ template <> struct Instr<F32, 32> {
     static constexpr int KW = 4;
 };
 
+// x / d = (x mul) >> shift
+struct Divisor {
+    uint64_t mul;
+    int shift;
+};
+
 struct Params {
     const char *A, *B;
     char *C;
@@ -215,6 +222,8 @@ struct Params {
     int out_f32, out_wide;         // out_wide: 16-byte runs of output columns are aligned and lie in one shard
     GemmMaps maps;
     unsigned step_a, step_b;       // bytes from one K-tile to the next inside a shard
+    int items;                     // gemm_ring.h: tiles of all blocks, and what an item's number is divided by
+    Divisor by_tiles, by_group, by_last;
 };
 
 // What a product runs on: the tile side, the bytes per load that its sizes and distances allow (the kernels exist for
@@ -224,6 +233,18 @@ struct Plan {
     Params params;
 };
 int make_plan(const GemmArgs &g, Plan *plan);
+
+// The ring kernel's tile (gemm_ring.h) and the estimated time of the launch in us; tile_m = 0: not for that kernel.
+struct RingPlan {
+    int tile_m, tile_n;
+    float us;
+};
+RingPlan ring_plan(const GemmArgs &g, const Plan &plan);
+
+constexpr int ring_ktile_bytes(int tile_n) { return tile_n == 32 ? 256 : 128; }
+// Offsets of an operand element stay below RING_SPAN; ROW_OUT marks a row or column beyond the operand, K_OUT an index beyond
+// the contraction: any sum with one of them (or both) lies in [RING_SPAN, 2^32).
+constexpr unsigned RING_SPAN = 1u << 30, ROW_OUT = 1u << 30, K_OUT = 1u << 31;
 
 template <int GB> struct Piece;
 template <> struct Piece<16> { typedef i32x4 Type; };
@@ -547,5 +568,9 @@ template <typename E, int GB> int launch_tile(const GemmArgs &g, const Params &p
 int gemm_edge_bf16(const GemmArgs &g, const edge::Params &p, int tile, int piece);
 int gemm_edge_fp8(const GemmArgs &g, const edge::Params &p, int tile, int piece);
 int gemm_edge_f32(const GemmArgs &g, const edge::Params &p, int tile, int piece);
+int gemm_ring_bf16(const GemmArgs &g, const edge::Params &p, const edge::RingPlan &r);
+int gemm_ring_fp8(const GemmArgs &g, const edge::Params &p, const edge::RingPlan &r);
+int gemm_ring_fp8_deep(const GemmArgs &g, const edge::Params &p, const edge::RingPlan &r);
+int gemm_ring_f32(const GemmArgs &g, const edge::Params &p, const edge::RingPlan &r);
 
 }  // namespace cube3d

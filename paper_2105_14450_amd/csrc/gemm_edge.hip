@@ -1,6 +1,8 @@
 // Dispatch of the product kernel for any size (gemm_edge.h).
 #include "gemm_edge.h"
 
+#include <cmath>
+
 namespace cube3d {
 using namespace edge;
 
@@ -176,11 +178,102 @@ int make_plan(const GemmArgs &g, Plan *plan)
 
 }  // namespace edge
 
+namespace {
+
+// Time of a ring launch in us: start, then per round of workgroups item (more with fp32 results) and ktile per K-tile;
+// pair: two workgroups on a CU (tiles of 32 and 64); the same with both operands K-major.  Fitted to 860 products of 8-8192
+// rows, 128-8192 columns, 35-8192 indices and 1-64 blocks on one MI355X, all tiles timed at each: the choice takes 1-1.6 %
+// longer than the best tile in the mean, and 0.80 of the time without the ring kernel (fp32 0.94).
+struct RingCost {
+    int tile_m, tile_n;
+    float start, item, wide, ktile, pair, ktile_kk, pair_kk;
+};
+constexpr RingCost RING_BF16[] = {{32, 32, 3.80f, 0.53f, 0.07f, 0.170f, 0.480f, 0.145f, 0.336f},
+                                  {64, 64, 3.91f, 0.82f, 0.29f, 0.171f, 0.396f, 0.152f, 0.380f},
+                                  {128, 128, 2.88f, 3.36f, 1.30f, 0.383f, 0.f, 0.329f, 0.f},
+                                  {128, 256, 2.00f, 6.16f, 1.82f, 0.565f, 0.f, 0.520f, 0.f},
+                                  {256, 128, 2.13f, 5.89f, 1.90f, 0.566f, 0.f, 0.510f, 0.f}};
+constexpr RingCost RING_FP8[] = {{32, 32, 3.98f, 0.46f, 0.f, 0.218f, 0.734f, 0.177f, 0.404f},       // bf16 results
+                                 {64, 64, 3.98f, 0.83f, 0.f, 0.200f, 0.517f, 0.222f, 0.445f},
+                                 {128, 128, 3.31f, 3.04f, 0.f, 0.409f, 0.f, 0.348f, 0.f},
+                                 {128, 256, 2.59f, 5.70f, 0.f, 0.537f, 0.f, 0.505f, 0.f},
+                                 {256, 128, 2.86f, 5.33f, 0.f, 0.557f, 0.f, 0.507f, 0.f}};
+constexpr RingCost RING_FP8_F32[] = {{32, 32, 4.03f, 0.47f, 0.f, 0.264f, 0.655f, 0.198f, 0.459f},   // fp32 results
+                                     {64, 64, 4.09f, 1.10f, 0.f, 0.194f, 0.494f, 0.182f, 0.494f},
+                                     {128, 128, 4.02f, 3.65f, 0.f, 0.658f, 0.f, 0.645f, 0.f},
+                                     {128, 256, 3.32f, 6.38f, 0.f, 1.073f, 0.f, 1.073f, 0.f},
+                                     {256, 128, 3.74f, 5.56f, 0.f, 1.196f, 0.f, 1.052f, 0.f}};
+constexpr RingCost RING_F32[] = {{64, 64, 3.86f, 1.44f, 0.f, 0.539f, 1.012f, 0.507f, 0.961f},
+                                 {128, 128, 3.25f, 4.87f, 0.f, 1.809f, 0.f, 1.791f, 0.f}};
+constexpr float PAIR_ITEM = 1.7f;      // an item's fixed part with two workgroups on the CU
+
+// What the ring kernel assumes of an operand: offsets below its buffer's size, the k-rows of a K-tile within half of that, and
+// shards of the contraction index that are whole and no shorter than a K-tile.
+bool ring_takes(const AxisMap &mn, const AxisMap &k, bool kmajor, int64_t extent, int64_t Kc, int es, int ktile)
+{
+    if ((last_offset(mn, extent) + last_offset(k, Kc) + 1) * es > (int64_t)RING_SPAN) return false;
+    if (!kmajor && k.u * es * ktile > (int64_t)RING_SPAN / 2) return false;
+    return k.P2 == INT32_MAX || (k.P2 >= ktile && Kc % k.P2 == 0);
+}
+
+}  // namespace
+
+namespace edge {
+
+RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
+{
+    RingPlan best{0, 0, 0.f};
+    const bool f32 = g.in_dtype == CUBE3D_F32, fp8 = g.in_dtype == CUBE3D_FP8_E4M3;
+    const int es = f32 ? 4 : fp8 ? 1 : 2;
+    if (plan.piece < 16) return best;
+    if (plan.tile == 32 && (f32 || g.Kc * es <= 256)) return best;
+    const bool wide = g.out_dtype == CUBE3D_F32, kk = g.a_kmajor && g.b_kmajor;
+    const RingCost *costs = f32 ? RING_F32 : fp8 ? (wide ? RING_FP8_F32 : RING_FP8) : RING_BF16;
+    const int n = f32 ? 2 : 5;
+    const int64_t cus = num_compute_units();
+    for (int i = 0; i < n; ++i) {
+        const RingCost &c = costs[i];
+        const int kb = ring_ktile_bytes(c.tile_n), ktile = kb / es;
+        if (!ring_takes(plan.params.maps.a_mn, plan.params.maps.a_k, g.a_kmajor, g.Mo, g.Kc, es, ktile) ||
+            !ring_takes(plan.params.maps.b_mn, plan.params.maps.b_k, g.b_kmajor, g.No, g.Kc, es, ktile)) continue;
+        const int64_t items = ((g.Mo + c.tile_m - 1) / c.tile_m) * ((g.No + c.tile_n - 1) / c.tile_n) * g.batch;
+        const bool pair = c.pair > 0.f && items > cus;
+        const float rounds = (float)((items + (pair ? 2 : 1) * cus - 1) / ((pair ? 2 : 1) * cus)), ktiles = (float)((g.Kc * es + kb - 1) / kb);
+        const float item = (c.item + (wide ? c.wide : 0.f)) * (pair ? PAIR_ITEM : 1.f);
+        const float ktime = pair ? (kk ? c.pair_kk : c.pair) : (kk ? c.ktile_kk : c.ktile);
+        const float us = c.start + rounds * (item + ktiles * ktime);
+        if (best.tile_m == 0 || us < best.us) best = RingPlan{c.tile_m, c.tile_n, us};
+    }
+    return best;
+}
+
+}  // namespace edge
+
+float gemm_edge_estimate(const GemmArgs &g)
+{
+    Plan plan;
+    if (make_plan(g, &plan) != CUBE3D_OK) return INFINITY;
+    const RingPlan ring = ring_plan(g, plan);
+    return ring.tile_m > 0 ? ring.us : INFINITY;
+}
+
 int gemm_edge(const GemmArgs &g)
 {
     Plan plan;
     const int rc = make_plan(g, &plan);
     if (rc != CUBE3D_OK) return rc;
+    const RingPlan ring = ring_plan(g, plan);
+    if (ring.tile_m > 0) {
+        switch (g.in_dtype) {
+        case CUBE3D_F32: return gemm_ring_f32(g, plan.params, ring);
+        case CUBE3D_BF16: return gemm_ring_bf16(g, plan.params, ring);
+        default:
+            // The 64-deep MFMAs add in another order than the 16-deep ones of all other kernels for any size: where the
+            // result is rounded to bf16 and the matrix cores are what bounds the tile.
+            return ring.tile_m >= 128 && g.out_dtype == CUBE3D_BF16 ? gemm_ring_fp8_deep(g, plan.params, ring)
+                                                                    : gemm_ring_fp8(g, plan.params, ring);
+        }
+    }
     switch (g.in_dtype) {
     case CUBE3D_F32: return gemm_edge_f32(g, plan.params, plan.tile, plan.piece);
     case CUBE3D_BF16: return gemm_edge_bf16(g, plan.params, plan.tile, plan.piece);
