@@ -26,6 +26,14 @@ bool map_ok(const AxisMap &m, int64_t extent, int64_t stride_align, bool contigu
     return m.s1 % stride_align == 0 && m.s2 % stride_align == 0;
 }
 
+// The figures are those of one MI355X under this kernel (shader clock 1.5-2.3 GHz depending on the
+// data): a 64-byte K-tile takes a workgroup 1024 MFMA cycles at 256 x 256 and 256 at 128 x 128; start-up,
+// first loads and epilogue of a workgroup 4 us; the reduction launch 3 us plus its traffic at
+// 2.5 TB/s (short launches do not reach more).  They only rank split counts; a device twice as fast
+// in everything picks the same plan.
+constexpr double T_KTILE_256_US = 0.44, T_KTILE_128_US = 0.14, T_WORKGROUP_US = 4.0, T_REDUCE_LAUNCH_US = 3.0,
+                 REDUCE_BYTES_PER_US = 2.5e6;
+
 // Pure function of the shape, so that cube3d_workspace_bytes() and the launch agree.
 Plan make_plan(const GemmArgs &g)
 {
@@ -56,6 +64,9 @@ Plan make_plan(const GemmArgs &g)
         const bool f256 = g.Mo % 256 == 0 && g.No % 256 == 0, f128 = !fp8 && g.Mo % 128 == 0 && g.No % 128 == 0;
         if (!f256 && !f128) return p;
         p.tile = (f256 && ((g.Mo / 256) * (g.No / 256) >= (3 * NUM_CU) / 4 || !f128)) ? 256 : 128;
+        const int64_t few = (g.Mo / p.tile) * (g.No / p.tile);
+        const double t = (double)(g.Kc / (64 / es)) * (p.tile == 128 ? T_KTILE_128_US : T_KTILE_256_US) + T_WORKGROUP_US;
+        if (2 * few <= NUM_CU && gemm_edge_estimate(g) < t) p.tile = 0;      // (as below)
         return p;
     }
     if (g.lda % align || g.ldb % align || g.strideA % align || g.strideB % align) return p;
@@ -81,13 +92,6 @@ Plan make_plan(const GemmArgs &g)
     // count from measured figures (microseconds: K-tile time per workgroup, fixed cost of a workgroup,
     // fixed cost and bandwidth of the reduction), smallest estimate wins.
     const int64_t tiles = (g.Mo / p.tile) * (g.No / p.tile) * g.batch;
-    // The figures are those of one MI355X under this kernel (shader clock 1.5-2.3 GHz depending on the
-    // data): a 64-byte K-tile takes a workgroup 1024 MFMA cycles at 256 x 256 and 256 at 128 x 128; start-up,
-    // first loads and epilogue of a workgroup 4 us; the reduction launch 3 us plus its traffic at
-    // 2.5 TB/s (short launches do not reach more).  They only rank split counts; a device twice as fast
-    // in everything picks the same plan.
-    constexpr double T_KTILE_256_US = 0.44, T_KTILE_128_US = 0.14, T_WORKGROUP_US = 4.0, T_REDUCE_LAUNCH_US = 3.0,
-                     REDUCE_BYTES_PER_US = 2.5e6;
     const double t_ktile = p.tile == 128 ? T_KTILE_128_US : T_KTILE_256_US, t_wg = T_WORKGROUP_US, t_reduce = T_REDUCE_LAUNCH_US,
                  bytes_per_us = REDUCE_BYTES_PER_US;
     const double out_bytes = (double)g.Mo * g.No * g.batch;
@@ -106,6 +110,8 @@ Plan make_plan(const GemmArgs &g)
     }
     if ((int64_t)g.batch * splits > 65535) splits = 1;
     p.splits = splits;
+    // Half of the CUs or more without a tile: smaller tiles take less time
+    if (splits == 1 && 2 * tiles <= NUM_CU && gemm_edge_estimate(g) < best) p.tile = 0;
     return p;
 }
 
