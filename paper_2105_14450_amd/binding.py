@@ -168,13 +168,23 @@ def _ptr(t):
         raise ValueError("device tensors only")
     if not t.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
+    """Handle of a stream, or of the calling thread's current one.  Building torch's Stream object for the latter takes
+    3.0 us of a call's 7.4 (3.0 are the launch); the handle alone 0.2."""
+    if stream is not None:
+        return stream.cuda_stream
+    return _raw_current_stream()
+
+
+def _raw_current_stream():
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:      # a torch without these
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _check(rc, where):

@@ -208,12 +208,13 @@ constexpr RingCost RING_F32[] = {{64, 64, 3.86f, 1.44f, 0.f, 0.539f, 1.012f, 0.5
 constexpr float PAIR_ITEM = 1.7f;      // an item's fixed part with two workgroups on the CU
 
 // What the ring kernel assumes of an operand: offsets below its buffer's size, the k-rows of a K-tile within half of that, and
-// shards of the contraction index that are whole and no shorter than a K-tile.
-bool ring_takes(const AxisMap &mn, const AxisMap &k, bool kmajor, int64_t extent, int64_t Kc, int es, int ktile)
+// shards of the contraction index that are whole and no shorter than a K-tile.  The longest K-tile that fits, in indices.
+int64_t longest_ring_ktile(const AxisMap &mn, const AxisMap &k, bool kmajor, int64_t extent, int64_t Kc, int es)
 {
-    if ((last_offset(mn, extent) + last_offset(k, Kc) + 1) * es > (int64_t)RING_SPAN) return false;
-    if (!kmajor && k.u * es * ktile > (int64_t)RING_SPAN / 2) return false;
-    return k.P2 == INT32_MAX || (k.P2 >= ktile && Kc % k.P2 == 0);
+    if ((last_offset(mn, extent) + last_offset(k, Kc) + 1) * es > (int64_t)RING_SPAN) return 0;
+    int64_t longest = kmajor ? INT32_MAX : (int64_t)RING_SPAN / 2 / (k.u * es);
+    if (k.P2 != INT32_MAX) longest = Kc % k.P2 ? 0 : longest < k.P2 ? longest : k.P2;
+    return longest;
 }
 
 }  // namespace
@@ -231,11 +232,13 @@ RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
     const RingCost *costs = f32 ? RING_F32 : fp8 ? (wide ? RING_FP8_F32 : RING_FP8) : RING_BF16;
     const int n = f32 ? 2 : 5;
     const int64_t cus = num_compute_units();
+    const GemmMaps &m = plan.params.maps;
+    const int64_t longest_a = longest_ring_ktile(m.a_mn, m.a_k, g.a_kmajor, g.Mo, g.Kc, es);
+    const int64_t longest_b = longest_ring_ktile(m.b_mn, m.b_k, g.b_kmajor, g.No, g.Kc, es);
     for (int i = 0; i < n; ++i) {
         const RingCost &c = costs[i];
-        const int kb = ring_ktile_bytes(c.tile_n), ktile = kb / es;
-        if (!ring_takes(plan.params.maps.a_mn, plan.params.maps.a_k, g.a_kmajor, g.Mo, g.Kc, es, ktile) ||
-            !ring_takes(plan.params.maps.b_mn, plan.params.maps.b_k, g.b_kmajor, g.No, g.Kc, es, ktile)) continue;
+        const int kb = ring_ktile_bytes(c.tile_n);
+        if (kb / es > longest_a || kb / es > longest_b) continue;
         const int64_t items = ((g.Mo + c.tile_m - 1) / c.tile_m) * ((g.No + c.tile_n - 1) / c.tile_n) * g.batch;
         const bool pair = c.pair > 0.f && items > cus;
         const float rounds = (float)((items + (pair ? 2 : 1) * cus - 1) / ((pair ? 2 : 1) * cus)), ktiles = (float)((g.Kc * es + kb - 1) / kb);
