@@ -10,8 +10,8 @@
 //
 // What bounds it (bf16, cycles per 128 bytes of contraction at 2.3 GHz).  Tiles of 64: the load path, 256 of 300.  Tiles of
 // 128: 512 for the loads and 512 for the MFMAs, 700.  256 x 128: MFMAs, 1024 of 1150-1250, and one or a few tiles per CU.
-// 8000 x 8192 x 2048: 241 us = 1.11 PFLOP/s, 318 in gemm_edge.h; three fp8 products of 3000 x 3072 x 12288 386 us = 1.76
-// PFLOP/s against 585.  Few rows (64 x 8192 x 2048 14.6 -> 11, 64 x 2048 x 8192 24 -> 21): one workgroup's K loop.
+// 8000 x 8192 x 2048: 225-240 us = 1.12-1.19 PFLOP/s, 318 in gemm_edge.h; three fp8 products of 3000 x 3072 x 12288 331 us =
+// 2.05 PFLOP/s against 585.  Few rows (64 x 8192 x 2048 14.6 -> 11, 64 x 2048 x 8192 24 -> 21): one workgroup's K loop.
 //
 // Edges.  The loads go through a buffer descriptor of 1 GiB: an offset beyond it reads as zeros, so rows beyond the
 // output, indices beyond the contraction and K-tiles beyond the last one are loads like any other, and the number of loads
@@ -109,6 +109,9 @@ __device__ __forceinline__ unsigned scalar(unsigned x)
     return y;
 }
 
+// Place of index x inside its shard (a prepared map).
+__device__ __forceinline__ int place_in_shard(const AxisMap &m, int x) { return x - (int)(((uint64_t)(unsigned)x * m.M2) >> m.N2) * m.P2; }
+
 // One operand's share of a wavefront: where its lanes read, and the walk along the contraction index.
 template <typename E, int T, int BKB, bool KM> struct RingOperand {
     static constexpr int EPS = 16 / E::ELT, TK = BKB / E::ELT;
@@ -203,11 +206,12 @@ template <> struct RingInstr<Fp8, 32> { typedef Fp8::M16 M; };
 // holds row lane % SIDE and columns 8 (v / 4) + 4 (lane / SIDE) + v % 4 of a block (operands exchanged in the MFMA) and
 // stores 16 consecutive bytes of a row.  The 16-byte slots of a strip row are permuted by the row, so that neither side has
 // bank conflicts.
-template <typename M, int NBM, int NBN, int OES, bool BIAS> struct RingOutput {
+template <typename M, int NBM, int NBN, int OES, bool BIAS, bool STREAM> struct RingOutput {
     static constexpr int SIDE = M::SIDE, VALS = SIDE * SIDE / 64;
     static constexpr int JH = OES == 2 && NBN % 2 == 0 ? 2 : 1;
     static constexpr int ROWB = JH * SIDE * OES, LPR = ROWB / 16, RPP = 64 / LPR < SIDE ? 64 / LPR : SIDE;    // bytes and lanes of a strip row, rows per pass
     static constexpr int BYTES = SIDE * ROWB;
+    static constexpr bool LARGEST = NBM * NBN > 4;      // tiles above 128 x 128
 
     __device__ static __forceinline__ int perm(int row) { return (row * ROWB / 256) % LPR; }
 
@@ -217,13 +221,24 @@ template <typename M, int NBM, int NBN, int OES, bool BIAS> struct RingOutput {
         asm volatile("" : "+v"(lane));
         const int g = lane / SIDE, in_side = lane % SIDE, rd_row = lane / LPR, rd_slot = lane % LPR;
         char *C = p.C + batch * p.sC;
+        const int64_t row_step = p.maps.c_m.u;
 #pragma unroll
         for (int jh = 0; jh < NBN; jh += JH) {
             const int col = n0 + jh * SIDE + rd_slot * (16 / OES);
             const int64_t col_off = col < p.No ? axis_offset_fast(p.maps.c_n, col) : 0;
-            float lane_bias = 0.f;      // of column `lane` of the strip
-            if (BIAS && lane < JH * SIDE && n0 + jh * SIDE + lane < p.No)
-                lane_bias = p.maps.bias[axis_offset_fast(p.maps.bias_n, n0 + jh * SIDE + lane)];
+            // the bias of this lane's columns, by way of the strip
+            f32x4 bias[JH][VALS / 4];
+            if constexpr (BIAS) {
+                if (lane < JH * SIDE) {
+                    const int c = n0 + jh * SIDE + lane;
+                    reinterpret_cast<float *>(strip)[lane] = c < p.No ? p.maps.bias[axis_offset_fast(p.maps.bias_n, c)] : 0.f;
+                }
+#pragma unroll
+                for (int j = 0; j < JH; ++j)
+#pragma unroll
+                    for (int v = 0; v < VALS; v += 4)
+                        bias[j][v / 4] = *reinterpret_cast<const f32x4 *>(strip + (j * SIDE + 2 * v + 4 * g) * 4);
+            }
 #pragma unroll
             for (int i = 0; i < NBM; ++i) {
 #pragma unroll
@@ -232,30 +247,39 @@ template <typename M, int NBM, int NBN, int OES, bool BIAS> struct RingOutput {
                     for (int v = 0; v < VALS; v += 4) {
                         float x[4];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float bias = BIAS ? __shfl(lane_bias, j * SIDE + 2 * v + 4 * g + e) : 0.f;
-                            x[e] = acc[i][jh + j][v + e] * p.alpha + bias;
-                        }
+                        for (int e = 0; e < 4; ++e) x[e] = acc[i][jh + j][v + e] * p.alpha + (BIAS ? bias[j][v / 4][e] : 0.f);
                         const int byte = (j * SIDE + 2 * v + 4 * g) * OES;
                         char *dst = strip + in_side * ROWB + (((byte / 16) ^ perm(in_side)) * 16) + byte % 16;
                         if constexpr (OES == 4) *reinterpret_cast<f32x4 *>(dst) = f32x4{x[0], x[1], x[2], x[3]};
                         else *reinterpret_cast<i32x2 *>(dst) = i32x2{(int)pack_bf16x2(x[0], x[1]), (int)pack_bf16x2(x[2], x[3])};
                     }
+                // largest tiles: the strip's rows mostly lie in one shard, then one division does for all of them
+                const int first = m0 + i * SIDE;
+                const bool one_shard = LARGEST && place_in_shard(p.maps.c_m, first) + SIDE <= p.maps.c_m.P2;
+                const int64_t first_off = one_shard ? axis_offset_fast(p.maps.c_m, first) : 0;
+                if (p.out_wide) {
 #pragma unroll
-                for (int ps = 0; ps < SIDE / RPP; ++ps) {
-                    const int r = ps * RPP + rd_row, row = m0 + i * SIDE + r;
-                    const i32x4 x = *reinterpret_cast<const i32x4 *>(strip + r * ROWB + ((rd_slot ^ perm(r)) * 16));
-                    if (row >= p.Mo || col >= p.No || r >= SIDE) continue;
-                    const int64_t row_off = axis_offset_fast(p.maps.c_m, row);
-                    if (p.out_wide) *reinterpret_cast<i32x4 *>(C + (row_off + col_off) * OES) = x;
-                    else {
-#pragma unroll
-                        for (int e = 0; e < 16 / OES; ++e)
-                            if (col + e < p.No) {
-                                const int64_t at = row_off + axis_offset_fast(p.maps.c_n, col + e);
-                                if constexpr (OES == 4) reinterpret_cast<int *>(C)[at] = x[e];
-                                else reinterpret_cast<unsigned short *>(C)[at] = (unsigned short)((unsigned)x[e / 2] >> (16 * (e % 2)));
-                            }
+                    for (int ps = 0; ps < SIDE / RPP; ++ps) {
+                        const int r = ps * RPP + rd_row, row = first + r;
+                        const i32x4 x = *reinterpret_cast<const i32x4 *>(strip + r * ROWB + ((rd_slot ^ perm(r)) * 16));
+                        if (row >= p.Mo || col >= p.No || r >= SIDE) continue;
+                        const int64_t row_off = one_shard ? first_off + r * row_step : axis_offset_fast(p.maps.c_m, row);
+                        i32x4 *dst = reinterpret_cast<i32x4 *>(C + (row_off + col_off) * OES);
+                        if (STREAM) __builtin_nontemporal_store(x, dst);
+                        else *dst = x;
+                    }
+                } else {        // element by element, rolled up: the instruction cache holds 64 KB
+#pragma unroll 1
+                    for (int r = rd_row; r < SIDE; r += RPP) {
+                        if (first + r >= p.Mo) break;
+                        const int64_t row_off = axis_offset_fast(p.maps.c_m, first + r);
+                        const char *src = strip + r * ROWB + ((rd_slot ^ perm(r)) * 16);
+#pragma unroll 1
+                        for (int e = 0; e < 16 / OES && col + e < p.No; ++e) {
+                            char *dst = C + (row_off + axis_offset_fast(p.maps.c_n, col + e)) * OES;
+                            if constexpr (OES == 4) *reinterpret_cast<int *>(dst) = *reinterpret_cast<const int *>(src + 4 * e);
+                            else *reinterpret_cast<unsigned short *>(dst) = *reinterpret_cast<const unsigned short *>(src + 2 * e);
+                        }
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);      // (one strip at a time: else registers for all of them)
@@ -269,8 +293,8 @@ constexpr int ring_strip(int TN) { return TN == 32 ? 16 * 16 * 4 : 32 * 32 * 4; 
 constexpr int ring_lds(int TM, int TN, int NST) { return NST * (TM + TN) * ring_ktile_bytes(TN) + 4 * ring_strip(TN); }
 constexpr int ring_per_cu(int TM, int TN, int NST) { return ring_lds(TM, TN, NST) > 80 * 1024 ? 1 : 2; }
 
-// Persistent workgroups: workgroup w makes the tiles w, w + gridDim.x, ...
-template <typename E, int TM, int TN, int NST, bool AK, bool BK>
+// Persistent workgroups: workgroup w makes the tiles w, w + gridDim.x, ...  STREAM: streaming stores of the output.
+template <typename E, int TM, int TN, int NST, bool AK, bool BK, bool STREAM>
 __global__ __launch_bounds__(512, 2 * ring_per_cu(TM, TN, NST)) void gemm_ring_kernel(const Params p)
 {
     constexpr int BKB = ring_ktile_bytes(TN);
@@ -287,7 +311,7 @@ __global__ __launch_bounds__(512, 2 * ring_per_cu(TM, TN, NST)) void gemm_ring_k
     static_assert(UNITS == 1 || UNITS % 2 == 0, "the fragment buffers alternate per unit");
     static_assert((NST - 1) * LPT <= 63, "vmcnt range");
     constexpr int STRIP = ring_strip(TN);
-    static_assert(RingOutput<M, NBM, NBN, 2, false>::BYTES <= STRIP && RingOutput<M, NBM, NBN, 4, false>::BYTES <= STRIP, "room for the output strips");
+    static_assert(RingOutput<M, NBM, NBN, 2, false, STREAM>::BYTES <= STRIP && RingOutput<M, NBM, NBN, 4, false, STREAM>::BYTES <= STRIP, "room for the output strips");
     typedef std::integral_constant<int, 2> I2;
     typedef std::integral_constant<int, 4> I4;
     __shared__ __attribute__((aligned(1024))) char smem[ring_lds(TM, TN, NST)];
@@ -432,7 +456,7 @@ __global__ __launch_bounds__(512, 2 * ring_per_cu(TM, TN, NST)) void gemm_ring_k
         }
         const Place at = place_item(p, item, TM, TN);
         auto store = [&](auto oes, auto bias) {
-            RingOutput<M, NBM, NBN, decltype(oes)::value, decltype(bias)::value>::store(p, acc, strip, at.m0 + wm, at.n0 + wn, at.batch, lane);
+            RingOutput<M, NBM, NBN, decltype(oes)::value, decltype(bias)::value, STREAM>::store(p, acc, strip, at.m0 + wm, at.n0 + wn, at.batch, lane);
         };
         // (a bias comes with the layout of the forward product, K-major times MN-major)
         if (AK && !BK && p.maps.bias != nullptr) p.out_f32 ? store(I4{}, yes) : store(I2{}, yes);
@@ -463,10 +487,20 @@ template <typename E, int TM, int TN, int NST> int ring_layout(const GemmArgs &g
     p.by_group = make_divisor(p.group_m * p.tiles_n);
     p.by_last = make_divisor(p.tiles_m % p.group_m ? p.tiles_m % p.group_m : p.group_m);
     const dim3 grid((unsigned)(items < places ? items : places)), block(512);
-    if (g.a_kmajor && g.b_kmajor) hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, true, true>), grid, block, 0, g.stream, p);
-    else if (g.a_kmajor) hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, true, false>), grid, block, 0, g.stream, p);
-    else hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, false, false>), grid, block, 0, g.stream, p);
-    return launch_status();
+    auto launch = [&](auto stream) {
+        constexpr bool S = decltype(stream)::value;
+        if (g.a_kmajor && g.b_kmajor) hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, true, true, S>), grid, block, 0, g.stream, p);
+        else if (g.a_kmajor) hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, true, false, S>), grid, block, 0, g.stream, p);
+        else hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, false, false, S>), grid, block, 0, g.stream, p);
+        return launch_status();
+    };
+    // Results that would take half of the eight 4 MB L2s from the operands' panels are written past them: three fp8 products of
+    // 3000 x 3072 x 12288 389 -> 363 us, 27 blocks of 1000 x 1536 x 512 63 -> 57.  Smaller ones the next call finds in the caches: an
+    // fp8 layer whose partial products take 10 MB lost 2 % with streaming stores.
+    if constexpr (TM * TN > 128 * 128) {
+        if ((int64_t)p.Mo * p.No * g.batch * (p.out_f32 ? 4 : 2) > (16ll << 20)) return launch(std::true_type{});
+    }
+    return launch(std::false_type{});
 }
 
 template <typename E> int ring_small(const GemmArgs &g, const Params &p, const RingPlan &r)
