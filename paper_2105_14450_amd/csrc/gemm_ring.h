@@ -352,8 +352,9 @@ __global__ __launch_bounds__(512, 2 * ring_per_cu(TM, TN, NST)) void gemm_ring_k
         };
         start_item();
 #pragma unroll 1
-        for (int s = 0; s < NST; ++s) load();
-        ring_barrier<(NST - 1) * LPT>();
+        for (int s = 0; s < NST - 1; ++s) load();
+        ring_barrier<(NST - 2) * LPT>();      // K-tile 0 is there
+        load();
         const int total = ntiles * my_items;
         int left = total - NST;        // K-tiles still to load
         while (left > 0) {
