@@ -9,6 +9,8 @@
 // wavefront takes whole rows, its lanes stride over 16-byte pieces of the row; all
 // index decoding is wave-uniform.  All-gathers: blockIdx.z = SOURCE processor, whose
 // shard is read once and written to the q members of its group (cube_gather_kernel).
+#include <type_traits>
+
 #include "common.h"
 
 namespace cube3d {
@@ -307,19 +309,19 @@ template <typename P> __device__ __forceinline__ void stream_store_pack(P *p, co
 
 // Sum over the q partials of a reduce direction, fp32, ascending index, one rounding at the
 // store.  V elements per lane per step; the loads of up to four partials are in flight together.
-// STREAM: streaming loads and stores, for partials that cannot stay in the caches anyway.
-template <typename TIn, typename TOut, int V, bool STREAM>
+// STREAM: streaming loads and stores, for partials that cannot stay in the caches anyway.  RPW: rows per wavefront, one
+// after the other.
+template <typename TIn, typename TOut, int V, bool STREAM, int RPW>
 __global__ __launch_bounds__(256) void cube_reduce_kernel(CubeGeom g, int mode, int64_t rows,
                                                           const TIn *__restrict__ partials, TOut *__restrict__ shards,
                                                           const float *__restrict__ bias)
 {
-    constexpr int RPW = ROWS_PER_BLOCK / 4;
     constexpr int QU = 4;                     // partials loaded together
     const int r = blockIdx.z;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const Coords c = decode_rank(g, r);
-    const int64_t row0 = (int64_t)blockIdx.x * ROWS_PER_BLOCK + wave;
+    const int64_t row0 = (int64_t)blockIdx.x * (4 * RPW) + wave;
 
     int64_t seg, src0, src_step, src_ld, dst_ld, src_row0, src_col0;
     if (mode == MV_REDUCE_Y) {  // keep row panel b of the sum over b'
@@ -387,7 +389,6 @@ template <typename TIn, typename TOut>
 int launch_reduce(const CubeGeom &g, int mode, int64_t rows, int64_t seg, const void *partials, void *shards,
                   const float *bias, hipStream_t stream)
 {
-    dim3 grid((unsigned)((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK), 1, (unsigned)(g.q * g.q * g.q));
     const TIn *p = static_cast<const TIn *>(partials);
     TOut *s = static_cast<TOut *>(shards);
     // Partials larger than the 256 MB Infinity Cache are read once from HBM whatever the caches do:
@@ -395,12 +396,19 @@ int launch_reduce(const CubeGeom &g, int mode, int64_t rows, int64_t seg, const 
     // partials: 4.8 -> 5.1-5.4 TB/s); smaller ones may still be cache-resident from the producing kernel.
     const int64_t n = (int64_t)g.q * g.q * g.q;
     const bool streaming = n * g.q * rows * seg * (int64_t)sizeof(TIn) > (256ll << 20);
-    if (seg % 4 == 0 && streaming)
-        hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 4, true>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
-    else if (seg % 4 == 0)
-        hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 4, false>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
-    else
-        hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 1, false>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
+    auto launch = [&](auto rpw) {
+        constexpr int RPW = decltype(rpw)::value;
+        const dim3 grid((unsigned)((rows + 4 * RPW - 1) / (4 * RPW)), 1, (unsigned)n);
+        if (seg % 4 == 0 && streaming)
+            hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 4, true, RPW>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
+        else if (seg % 4 == 0)
+            hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 4, false, RPW>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
+        else
+            hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 1, false, RPW>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
+    };
+    // Four rows one after the other cost a wavefront four memory latencies: with fewer than eight workgroups per CU it takes one.
+    if (n * ((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) < 2048) launch(std::integral_constant<int, 1>{});
+    else launch(std::integral_constant<int, ROWS_PER_BLOCK / 4>{});
     return launch_status();
 }
 
