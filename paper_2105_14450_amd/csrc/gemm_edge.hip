@@ -181,30 +181,30 @@ int make_plan(const GemmArgs &g, Plan *plan)
 namespace {
 
 // Time of a ring launch in us: start, then per round of workgroups item (more with fp32 results) and ktile per K-tile;
-// pair: two workgroups on a CU (tiles of 32 and 64); the same with both operands K-major.  Fitted to 860 products of 8-8192
-// rows, 128-8192 columns, 35-8192 indices and 1-64 blocks on one MI355X, all tiles timed at each: the choice takes 1-1.6 %
-// longer than the best tile in the mean, and 0.80 of the time without the ring kernel (fp32 0.94).
+// pair: two workgroups on a CU (tiles of 32 and 64); the same with both operands K-major.  Fitted to 810 products of 8-8192
+// rows, 128-8192 columns, 35-8192 indices and 1-64 blocks on one MI355X, all tiles timed at each: the choice takes 0.6-1.4 %
+// longer than the best tile in the mean, and less than 0.80 of the time without the ring kernel (fp32 0.94).
 struct RingCost {
     int tile_m, tile_n;
     float start, item, wide, ktile, pair, ktile_kk, pair_kk;
 };
-constexpr RingCost RING_BF16[] = {{32, 32, 3.80f, 0.53f, 0.07f, 0.170f, 0.480f, 0.145f, 0.336f},
-                                  {64, 64, 3.91f, 0.82f, 0.29f, 0.171f, 0.396f, 0.152f, 0.380f},
-                                  {128, 128, 2.88f, 3.36f, 1.30f, 0.383f, 0.f, 0.329f, 0.f},
-                                  {128, 256, 2.00f, 6.16f, 1.82f, 0.565f, 0.f, 0.520f, 0.f},
-                                  {256, 128, 2.13f, 5.89f, 1.90f, 0.566f, 0.f, 0.510f, 0.f}};
-constexpr RingCost RING_FP8[] = {{32, 32, 3.98f, 0.46f, 0.f, 0.218f, 0.734f, 0.177f, 0.404f},       // bf16 results
-                                 {64, 64, 3.98f, 0.83f, 0.f, 0.200f, 0.517f, 0.222f, 0.445f},
-                                 {128, 128, 3.31f, 3.04f, 0.f, 0.409f, 0.f, 0.348f, 0.f},
-                                 {128, 256, 2.59f, 5.70f, 0.f, 0.537f, 0.f, 0.505f, 0.f},
-                                 {256, 128, 2.86f, 5.33f, 0.f, 0.557f, 0.f, 0.507f, 0.f}};
-constexpr RingCost RING_FP8_F32[] = {{32, 32, 4.03f, 0.47f, 0.f, 0.264f, 0.655f, 0.198f, 0.459f},   // fp32 results
-                                     {64, 64, 4.09f, 1.10f, 0.f, 0.194f, 0.494f, 0.182f, 0.494f},
-                                     {128, 128, 4.02f, 3.65f, 0.f, 0.658f, 0.f, 0.645f, 0.f},
-                                     {128, 256, 3.32f, 6.38f, 0.f, 1.073f, 0.f, 1.073f, 0.f},
-                                     {256, 128, 3.74f, 5.56f, 0.f, 1.196f, 0.f, 1.052f, 0.f}};
-constexpr RingCost RING_F32[] = {{64, 64, 3.86f, 1.44f, 0.f, 0.539f, 1.012f, 0.507f, 0.961f},
-                                 {128, 128, 3.25f, 4.87f, 0.f, 1.809f, 0.f, 1.791f, 0.f}};
+constexpr RingCost RING_BF16[] = {{32, 32, 3.67f, 0.52f, 0.06f, 0.166f, 0.485f, 0.146f, 0.335f},
+                                  {64, 64, 3.69f, 0.80f, 0.27f, 0.165f, 0.389f, 0.150f, 0.370f},
+                                  {128, 128, 2.65f, 3.15f, 1.26f, 0.374f, 0.f, 0.333f, 0.f},
+                                  {128, 256, 2.34f, 5.30f, 2.37f, 0.558f, 0.f, 0.519f, 0.f},
+                                  {256, 128, 2.59f, 4.97f, 2.41f, 0.560f, 0.f, 0.510f, 0.f}};
+constexpr RingCost RING_FP8[] = {{32, 32, 3.76f, 0.47f, 0.00f, 0.234f, 0.736f, 0.213f, 0.427f},       // bf16 results
+                                 {64, 64, 3.75f, 0.84f, 0.00f, 0.224f, 0.532f, 0.251f, 0.495f},
+                                 {128, 128, 2.95f, 2.91f, 0.00f, 0.396f, 0.f, 0.345f, 0.f},
+                                 {128, 256, 2.71f, 4.93f, 0.00f, 0.528f, 0.f, 0.523f, 0.f},
+                                 {256, 128, 2.90f, 4.69f, 0.00f, 0.548f, 0.f, 0.526f, 0.f}};
+constexpr RingCost RING_FP8_F32[] = {{32, 32, 3.82f, 0.47f, 0.00f, 0.234f, 0.675f, 0.208f, 0.459f},   // fp32 results
+                                     {64, 64, 3.66f, 1.11f, 0.00f, 0.235f, 0.488f, 0.244f, 0.532f},
+                                     {128, 128, 2.58f, 4.20f, 0.00f, 0.548f, 0.f, 0.559f, 0.f},
+                                     {128, 256, 3.00f, 6.40f, 0.00f, 0.999f, 0.f, 0.989f, 0.f},
+                                     {256, 128, 3.18f, 6.12f, 0.00f, 0.981f, 0.f, 0.893f, 0.f}};
+constexpr RingCost RING_F32[] = {{64, 64, 3.63f, 1.40f, 0.00f, 0.535f, 1.016f, 0.508f, 0.925f},
+                                 {128, 128, 2.52f, 5.02f, 0.00f, 1.801f, 0.f, 1.801f, 0.f}};
 constexpr float PAIR_ITEM = 1.7f;      // an item's fixed part with two workgroups on the CU
 
 // What the ring kernel assumes of an operand: offsets below its buffer's size, the k-rows of a K-tile within half of that, and
