@@ -227,6 +227,9 @@ RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
     const bool f32 = g.in_dtype == CUBE3D_F32, fp8 = g.in_dtype == CUBE3D_FP8_E4M3;
     const int es = f32 ? 4 : fp8 ? 1 : 2;
     if (plan.piece < 16) return best;
+    if (plan.params.maps.bias && (!g.a_kmajor || g.b_kmajor)) return best;     // the ring adds a bias in the forward layout only
+    // Few rows in fp32: the wavefronts of a 32 x 32 tile share its k-steps, a quarter of the chain (10 x 384 x 3904: 28 us, 69 on
+    // the ring's tiles of 64).  One K-tile of 256 bytes: nothing to keep in flight (85 x 448 x 128 fp8 4.5 against 4.7 us).
     if (plan.tile == 32 && (f32 || g.Kc * es <= 256)) return best;
     const bool wide = g.out_dtype == CUBE3D_F32, kk = g.a_kmajor && g.b_kmajor;
     const RingCost *costs = f32 ? RING_F32 : fp8 ? (wide ? RING_FP8_F32 : RING_FP8) : RING_BF16;
