@@ -24,15 +24,17 @@
 //
 // Sums.  As in gemm_edge.h: all products of an element in ascending order in one accumulator (fp32: four of every eight
 // indices alternately), and the same bits.  fp8 with bf16 results takes the 64-deep MFMA in tiles of 128 and more, twice as
-// fast: before the rounding one sum in a million differs in its last bit (N(0,1) operands, 2048 indices), the error
-// against 64 bits is the same to six digits.
+// fast, with its operands laid out so that it adds in that order too (Fp8Deep).
 #pragma once
 #include "gemm_edge.h"
 
 namespace cube3d {
 namespace edge {
 
-// fp8 with the 64-deep MFMA (a lane half holds a consecutive run of 32 contraction indices)
+// fp8 with the 64-deep MFMA.  It adds 16 products at a time: the lower 16 bytes of lanes 0-31, those of lanes 32-63, then
+// the upper 16 bytes of either.  Dealt out in that order the contraction indices are added as by four 16-deep MFMAs, to the
+// last bit (524288 sums of 64, 512 and 4096 products of random bytes: none differs; with a run of 32 indices per lane half
+// 2, 19 and 62 % of them do), so a row's bits do not depend on the tile here either.
 struct Fp8Deep {
     static constexpr int ELT = 1;
     __device__ static __forceinline__ int mn_swz(int k, int spr) { return Fp8::mn_swz(k, spr); }
@@ -42,9 +44,9 @@ struct Fp8Deep {
         typedef f32x16 Acc;
         __device__ static __forceinline__ Frag read_k(const char *row, int swz, int step, int g)
         {
-            const int c = 4 * step + 2 * g;
+            const int c = 4 * step + g;
             const i32x4 lo = *reinterpret_cast<const i32x4 *>(row + ((c ^ swz) * 16));
-            const i32x4 hi = *reinterpret_cast<const i32x4 *>(row + (((c + 1) ^ swz) * 16));
+            const i32x4 hi = *reinterpret_cast<const i32x4 *>(row + (((c + 2) ^ swz) * 16));
             return Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         }
         template <int RB> __device__ static __forceinline__ Frag read_mn(const char *tile, int lane, int col0, int step)
@@ -53,7 +55,7 @@ struct Fp8Deep {
             Frag f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const i32x2 v = Fp8::read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0 + 16 * (g % 2), 32 * (g / 2) + 8 * i);
+                const i32x2 v = Fp8::read_mn_at<RB>(tile + step * KSTEP * RB, lane % 16, col0 + 16 * (g % 2), 32 * (i / 2) + 16 * (g / 2) + 8 * (i % 2));
                 f[2 * i] = v[0];
                 f[2 * i + 1] = v[1];
             }

@@ -66,7 +66,7 @@ def test_cube_in_place(q, M, K, N, dtype, out):
 # bf16 and fp8: every element adds its products in ascending order in one accumulator, whatever the tile, so the rows of a small
 # call are bit for bit those of a large one.  33 x 1040 outputs run on 32 x 32 tiles, 400 x 1600 on 64 x 64, 1808 x 1600
 # on 128 x 128; with k = 40 the largest runs element by element.
-@pytest.mark.parametrize("dtype,out", [("bf16", "f32"), ("bf16", "bf16"), ("fp8_e4m3", "f32")])
+@pytest.mark.parametrize("dtype,out", [("bf16", "f32"), ("bf16", "bf16"), ("fp8_e4m3", "f32"), ("fp8_e4m3", "bf16")])
 @pytest.mark.parametrize("k", [40, 488, 2000, 1001])
 @pytest.mark.parametrize("form", [c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB])
 def test_same_bits_for_every_number_of_rows(form, k, dtype, out):

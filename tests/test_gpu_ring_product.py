@@ -44,6 +44,38 @@ def test_ring_tiles(dtype, out, form):
             assert torch.equal(got, torch.bmm(a, b).to(got.dtype)), "%d x %d x %d" % (m, n, k)
 
 
+# fp8: tiles of 128 and more take the 64-deep MFMA for bf16 results, smaller ones and fp32 results the shallower ones.  A row's
+# bits do not depend on that: a call with bf16 results is one with fp32 results rounded once, and the rows of a call with
+# few rows are those of one with many.  Random bytes, whose sums depend on the order in nearly every element; against 64 bits
+# one rounding to bf16 and 1e-4 of the largest entry for the matrix cores' sums.
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", LAYOUT)
+@pytest.mark.parametrize("m,n,k", [(1616, 2064, 1040), (1136, 7152, 4112), (4112, 2064, 2064)])
+def test_fp8_bits_do_not_depend_on_the_tile(m, n, k, form):
+    gen = torch.Generator(device="cuda").manual_seed(m + form)
+
+    def codes(rows, cols):      # every one but the two NaNs
+        t = torch.randint(0, 254, (rows, cols), device="cuda", generator=gen, dtype=torch.int16)
+        return (t + (t >= 127)).to(torch.uint8)
+
+    def product(rows, out):
+        left = (a[:rows].t() if form == c3.FORM_ATB else a[:rows]).contiguous().view(torch.float8_e4m3fn)
+        right = (b.t() if form == c3.FORM_ABT else b).contiguous().view(torch.float8_e4m3fn)
+        mm = c3.make_matmul(1, form, rows, n, k, in_dtype=c3.FP8_E4M3, out_dtype=CODES[out][1])
+        got = torch.full((rows, n), float("nan"), device="cuda", dtype=CODES[out][0])
+        c3.cube3d_matmul_blocks(mm, left, right, got)
+        return got
+
+    a, b = codes(m, k), codes(k, n)
+    got = product(m, "bf16")
+    for rows in (400, 48):
+        assert torch.equal(product(rows, "bf16"), got[:rows]), rows
+    assert torch.equal(product(m, "f32").to(torch.bfloat16), got)
+    want = a.view(torch.float8_e4m3fn).double() @ b.view(torch.float8_e4m3fn).double()
+    bound = want.abs() / 256 + 1e-4 * want.abs().max()
+    assert bool(((got.double() - want).abs() <= bound).all())
+
+
 # q = 3: blocks of 3 shards that end inside a K-tile (of 64 to 256 indices), in every direction; a bias with the forward
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N", [(9 * 272, 3 * 656, 9 * 368), (9 * 304, 3 * 272, 9 * 272), (9 * 16, 3 * 1040, 9 * 272)])
