@@ -76,6 +76,33 @@ def test_fp8_bits_do_not_depend_on_the_tile(m, n, k, form):
     assert bool(((got.double() - want).abs() <= bound).all())
 
 
+# Tile-aligned fp8 products run on the tuned kernel with many rows and on the ring with few: the same bits too (no split of
+# the contraction at these sizes).  Random bytes; plain operands and a cube of one processor read in place.
+@pytest.mark.gpu
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+@pytest.mark.parametrize("form", LAYOUT)
+def test_fp8_bits_of_few_and_many_aligned_rows(form, out):
+    gen = torch.Generator(device="cuda").manual_seed(form)
+    m, n, k = 16384, 1024, 1024
+    t = torch.randint(0, 254, (m + n, k), device="cuda", generator=gen, dtype=torch.int16)
+    t = (t + (t >= 127)).to(torch.uint8)
+    a, b = t[:m], t[m:].t()
+    plain, in_place = {}, {}
+    for rows in (m, 256):
+        left = (a[:rows].t() if form == c3.FORM_ATB else a[:rows]).contiguous().view(torch.float8_e4m3fn)
+        right = (b.t() if form == c3.FORM_ABT else b).contiguous().view(torch.float8_e4m3fn)
+        mm = c3.make_matmul(1, form, rows, n, k, in_dtype=c3.FP8_E4M3, out_dtype=CODES[out][1])
+        assert c3.cube3d_matmul_workspace_bytes(mm) == 0
+        plain[rows], in_place[rows] = (torch.full((rows, n), float("nan"), device="cuda", dtype=CODES[out][0]) for _ in range(2))
+        c3.cube3d_matmul_blocks(mm, left, right, plain[rows])
+        x, y, z = c3.AXIS_X, c3.AXIS_Y, c3.AXIS_Z
+        stored = lambda shape, code: c3.make_matrix(1, *shape, x, y, c3.SPLIT_ROWS, code)
+        c3.virtual_cube_matmul(form, stored(left.shape, c3.FP8_E4M3), stored(right.shape, c3.FP8_E4M3), stored((rows, n), CODES[out][1]),
+                               left, right, in_place[rows], 1.0, 1.0)
+        assert torch.equal(plain[rows], in_place[rows]), rows
+    assert torch.equal(plain[m][:256], plain[256])
+
+
 # q = 3: blocks of 3 shards that end inside a K-tile (of 64 to 256 indices), in every direction; a bias with the forward
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N", [(9 * 272, 3 * 656, 9 * 368), (9 * 304, 3 * 272, 9 * 272), (9 * 16, 3 * 1040, 9 * 272)])
