@@ -1,6 +1,7 @@
 """Build ``libcube3d.so`` (the C-ABI library) for gfx950 with hipcc, in-tree."""
 import glob
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -62,11 +63,78 @@ def _spills_in_k_loops(asm_path):
     return sorted(set(bad))
 
 
+SCALAR_WAIT = 5     # wait states between a vector instruction that writes a scalar register and a memory instruction that reads it
+_SCALARS = re.compile(r"\bs(?:(\d+)|\[(\d+):(\d+)\])")
+_NO_RESULT = ("s_cmp", "s_bitcmp", "s_cbranch", "s_branch", "s_nop", "s_wait", "s_barrier", "s_setprio", "s_endpgm")
+
+
+def _scalars(operands):
+    return {r for one, first, last in _SCALARS.findall(operands)
+            for r in (range(int(first), int(last) + 1) if first else (int(one),))}
+
+
+def early_scalar_reads(asm):
+    """Loads straight into LDS (lines of device assembly) that may read a scalar register less than SCALAR_WAIT wait states
+    after a vector instruction wrote it: (kernel, writer, load).  They are inline assembly, where the compiler sees no memory
+    instruction and keeps no distance.  A copy by a scalar instruction is as good as the distance."""
+    found, kernel, code = [], None, []
+
+    def close():
+        loads = [i for i, x in enumerate(code) if "load" in x and (x.endswith(" lds") or "load_lds" in x)]
+        if not loads:
+            return
+        into = {}           # label -> branches to it
+        for i, x in enumerate(code):
+            if x.startswith(("s_cbranch", "s_branch")):
+                into.setdefault(x.split()[-1], []).append(i)
+
+        def before(i):
+            out = list(into.get(code[i][:-1], ())) if code[i].endswith(":") else []
+            if i > 0 and not code[i - 1].startswith(("s_branch", "s_endpgm")):
+                out.append(i - 1)
+            return out
+
+        for load in loads:
+            todo, seen = [(p, 0, frozenset(_scalars(code[load]))) for p in before(load)], set()
+            while todo:
+                state = i, waited, regs = todo.pop()
+                if waited >= SCALAR_WAIT or not regs or state in seen:
+                    continue
+                seen.add(state)
+                x = code[i]
+                if not x.endswith(":"):
+                    op, _, operands = x.partition(" ")
+                    result = operands.split(",")[0]
+                    if op.startswith("v_"):
+                        # (the second operand is a result too where there is a carry)
+                        if "_co_" in op or op.startswith(("v_mad_u64", "v_mad_i64", "v_div_scale")):
+                            result = ",".join(operands.split(",")[:2])
+                        if _scalars(result) & regs:
+                            found.append((kernel, x, code[load]))
+                    elif op.startswith("s_") and not op.startswith(_NO_RESULT):
+                        regs = regs - _scalars(result)
+                    waited += int(operands, 0) + 1 if op == "s_nop" else 1
+                todo += [(p, waited, regs) for p in before(i)]
+
+    for line in asm:
+        head = line.split(";")[0].strip()
+        if not head or head.startswith(".") and not head.startswith(".LBB"):
+            continue
+        if head.endswith(":") and not head.startswith("."):
+            close()
+            kernel, code = head[:-1], []
+        else:
+            code.append(" ".join(head.split()))
+    close()
+    return found
+
+
 def _compile(src):
     """Compile one source; refuse kernels that spill registers inside a K loop (the tuned kernels
     are sized to live in the register file: a spill there is a performance bug) or that spill
-    wholesale.  What the persistent kernel parks between two work items (lane-constant addresses,
-    a few dozen registers, reloaded once per item) is accepted."""
+    wholesale, and loads into LDS that may read a scalar register too early.  What the persistent
+    kernel parks between two work items (lane-constant addresses, a few dozen registers, reloaded
+    once per item) is accepted."""
     base = os.path.basename(src)
     obj = os.path.join(OBJDIR, base + ".o")
     res = subprocess.run([HIPCC, *FLAGS, "-Rpass-analysis=kernel-resource-usage", "-save-temps=obj", "-c", src, "-o", obj],
@@ -91,6 +159,10 @@ def _compile(src):
         glob.glob(os.path.join(OBJDIR, os.path.splitext(base)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s"))
     for path in asm:
         spilled += _spills_in_k_loops(path)
+        with open(path) as f:
+            early = early_scalar_reads(f)
+        if early:
+            raise RuntimeError("scalar registers read too early in %s: %d loads, first %s" % (base, len(early), early[0]))
     # (a profiling build carries the time stamps' registers as well: its spills are reported, not refused)
     if spilled and ("-DCUBE3D_PROFILE" in FLAGS or os.environ.get("CUBE3D_ALLOW_SPILLS")):
         sys.stderr.write("note: register spills in %s: %d kernels\n" % (base, len(set(spilled))))

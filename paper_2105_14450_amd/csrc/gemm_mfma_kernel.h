@@ -70,10 +70,14 @@ template <int N> __device__ __forceinline__ void tile_barrier()
 // with the 16 bytes at base + offset (scalar 64-bit base, 32-bit unsigned lane offset).
 // Issued as inline assembly so that its completion is tracked by the explicit
 // s_waitcnt vmcnt(..) + barrier of the pipeline and by nothing else (the compiler would
-// otherwise drain every outstanding load before each LDS read).
+// otherwise drain every outstanding load before each LDS read).  It does not see a memory instruction
+// here, so it does not keep the 5 wait states between a vector instruction that writes a scalar register (a spilled
+// base read back by v_readlane) and a load that reads it: the load takes the base from a copy made by
+// the scalar unit, which the hardware does wait for.  The copy is also the wait state behind the write of m0.
 __device__ __forceinline__ void async_load16(const char *base, unsigned offset, unsigned lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(offset), "s"(base), "s"(lds_base) : "m0");
+    const char *copy;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0" : "=&s"(copy) : "v"(offset), "s"(base), "s"(lds_base) : "m0");
 }
 
 // -1 if the two wavefront-uniform values are equal, else 0; opaque to the compiler, which would
