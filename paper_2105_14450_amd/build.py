@@ -23,9 +23,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
 
 SCRATCH_LIMIT = 1024   # bytes per lane
 # The any-size kernels' K loops span several basic blocks, which the search below does not recognise as loops: no
-# scratch at all (none of them needs any; two ring kernels reserve 20 bytes for scalar registers that end up in vector
-# registers, without an access).
-SCRATCH_LIMITS = {"gemm_edge_kernel": 0, "gemm_ring_kernel": 20}
+# scratch at all (none of them needs any).
+SCRATCH_LIMITS = {"gemm_edge_kernel": 0, "gemm_ring_kernel": 0}
 MFMA_BLOCK = 8         # a basic block with at least this many MFMAs belongs to a K loop
 
 

@@ -8,24 +8,24 @@ import pytest
 from paper_2105_14450_amd import build
 
 ALL_ASM = sorted(glob.glob(os.path.join(build.HERE, "_build", "*-hip-amdgcn-amd-amdhsa-gfx950.s")))
-ASM = sorted(glob.glob(os.path.join(build.HERE, "_build", "gemm_edge_*-hip-amdgcn-amd-amdhsa-gfx950.s")))
 
 
 def test_any_size_kernels_may_not_use_scratch_memory():
     assert build.scratch_limit("_ZN6cube3d4edge16gemm_edge_kernelINS0_4Bf16ELi128ELi2ELb1ELb0EEEvNS0_6ParamsE") == 0
+    assert build.scratch_limit("_ZN6cube3d4edge16gemm_ring_kernelINS0_4Bf16ELi256ELi128ELi3ELb1ELb1ELb0EEEvNS0_6ParamsE") == 0
     assert build.scratch_limit("_ZN6cube3d3mfk16gemm_mfma_kernelIvEEvv") == build.SCRATCH_LIMIT
 
 
-@pytest.mark.skipif(not ASM, reason="no assembly of a build here")
+@pytest.mark.skipif(not ALL_ASM, reason="no assembly of a build here")
 def test_any_size_kernels_use_no_scratch_memory():
-    seen = 0
-    for path in ASM:
+    seen = {"gemm_edge_kernel": 0, "gemm_ring_kernel": 0}
+    for path in ALL_ASM:
         with open(path) as f:
             text = f.read()
-        for name, size in re.findall(r"\.name: +(\S*gemm_edge_kernel\S*)\n(?:.*\n)*? *\.private_segment_fixed_size: (\d+)", text):
-            seen += 1
+        for name, kind, size in re.findall(r"\.name: +(\S*(gemm_edge_kernel|gemm_ring_kernel)\S*)\n(?:.*\n)*? *\.private_segment_fixed_size: (\d+)", text):
+            seen[kind] += 1
             assert int(size) == 0, name
-    assert seen == 69
+    assert seen == {"gemm_edge_kernel": 69, "gemm_ring_kernel": 63}
 
 
 LOAD = "\tglobal_load_lds_dwordx4 v1, s[44:45]"
