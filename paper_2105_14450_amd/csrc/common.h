@@ -125,6 +125,8 @@ float gemm_edge_estimate(const GemmArgs &g);
 
 // Tuned bf16 / fp8 path; returns CUBE3D_ENOTIMPL when the shape does not fit its tiles.
 int gemm_fast(const GemmArgs &g);
+// Tile side it takes the product with, 0 if it does not.
+int gemm_fast_tile(const GemmArgs &g);
 size_t gemm_fast_workspace(const GemmArgs &g);
 // Launch of the tuned kernel's map-addressed instantiations (tile = 256 or 128, chosen by gemm_fast).
 int gemm_fast_mapped(const GemmArgs &g, int tile);

@@ -240,6 +240,8 @@ struct RingPlan {
     float us;
 };
 RingPlan ring_plan(const GemmArgs &g, const Plan &plan);
+// Whether it writes the result with streaming stores.
+bool ring_streams(const GemmArgs &g, const Params &p, const RingPlan &r);
 
 constexpr int ring_ktile_bytes(int tile_n) { return tile_n == 32 ? 256 : 128; }
 // Offsets of an operand element stay below RING_SPAN; ROW_OUT marks a row or column beyond the operand, K_OUT an index beyond

@@ -253,6 +253,21 @@ RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
     return best;
 }
 
+// Results that would take half of the eight 4 MB L2s from the operands' panels are written past them: three fp8 products of
+// 3000 x 3072 x 12288 389 -> 363 us, 27 blocks of 1000 x 1536 x 512 63 -> 57.  Smaller ones the next call finds in the caches: an
+// fp8 layer whose partial products take 10 MB lost 2 % with streaming stores.  Only whole cache lines, that is where the 128
+// bytes that eight lanes of an output row store are one: 64 blocks of 2934 x 1608 x 80 with fp32 results, whose rows end inside
+// a line, took 697 us with streaming stores and 405 without.  Tiles above 128 x 128 only: 1-2 % lost with smaller ones.
+bool ring_streams(const GemmArgs &g, const Params &p, const RingPlan &r)
+{
+    const int es = p.out_f32 ? 4 : 2;
+    if (r.tile_m * r.tile_n <= 128 * 128 || g.Mo * g.No * g.batch * es <= (16ll << 20)) return false;
+    const AxisMap &m = p.maps.c_m, &n = p.maps.c_n;
+    for (int64_t x : {m.u, m.s1, m.s2, n.s1, n.s2})
+        if (x * es % 128) return false;
+    return n.u == 1 && (n.P2 == INT32_MAX || (int64_t)n.P2 * es % 128 == 0) && p.sC % 128 == 0 && (uintptr_t)p.C % 128 == 0;
+}
+
 }  // namespace edge
 
 float gemm_edge_estimate(const GemmArgs &g)

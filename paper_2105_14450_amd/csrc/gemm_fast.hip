@@ -186,6 +186,8 @@ size_t gemm_fast_workspace(const GemmArgs &g)
     return (size_t)g.batch * pl.splits * g.Mo * g.No * sizeof(float);
 }
 
+int gemm_fast_tile(const GemmArgs &g) { return make_plan(g).tile; }
+
 int gemm_fast(const GemmArgs &g)
 {
     const Plan pl = make_plan(g);

@@ -479,16 +479,6 @@ inline Divisor make_divisor(int d)
     return Divisor{m.M1, m.N1};
 }
 
-// Whether the 128 bytes that eight lanes of an output row store are one cache line.
-inline bool output_in_lines(const Params &p)
-{
-    const int es = p.out_f32 ? 4 : 2;
-    const AxisMap &m = p.maps.c_m, &n = p.maps.c_n;
-    for (int64_t x : {m.u, m.s1, m.s2, n.s1, n.s2})
-        if (x * es % 128) return false;
-    return n.u == 1 && (n.P2 == INT32_MAX || (int64_t)n.P2 * es % 128 == 0) && p.sC % 128 == 0 && (uintptr_t)p.C % 128 == 0;
-}
-
 template <typename E, int TM, int TN, int NST> int ring_layout(const GemmArgs &g, Params p)
 {
     p.tiles_m = (p.Mo + TM - 1) / TM;
@@ -509,12 +499,8 @@ template <typename E, int TM, int TN, int NST> int ring_layout(const GemmArgs &g
         else hipLaunchKernelGGL((gemm_ring_kernel<E, TM, TN, NST, false, false, S>), grid, block, 0, g.stream, p);
         return launch_status();
     };
-    // Results that would take half of the eight 4 MB L2s from the operands' panels are written past them: three fp8 products of
-    // 3000 x 3072 x 12288 389 -> 363 us, 27 blocks of 1000 x 1536 x 512 63 -> 57.  Smaller ones the next call finds in the caches: an
-    // fp8 layer whose partial products take 10 MB lost 2 % with streaming stores.  Only whole cache lines: 64 blocks of
-    // 2934 x 1608 x 80 with fp32 results, whose rows end inside a line, took 697 us with streaming stores and 405 without.
     if constexpr (TM * TN > 128 * 128) {
-        if ((int64_t)p.Mo * p.No * g.batch * (p.out_f32 ? 4 : 2) > (16ll << 20) && output_in_lines(p)) return launch(std::true_type{});
+        if (ring_streams(g, p, RingPlan{TM, TN, 0.f})) return launch(std::true_type{});
     }
     return launch(std::false_type{});
 }

@@ -1,8 +1,11 @@
 // Prints which kernel family, tile side and load width the library picks for products, one per line of standard input:
 //   plain <dtype> <out dtype> <a K-major> <b K-major> <batch> <Mo> <No> <Kc>
 //   cube  <dtype> <out dtype> <op: 0 forward, 1 dX, 2 dW> <q> <M> <K> <N>           (input gathered along y, no bias)
-// One line of output each: "tile piece" of the any-size kernel, or "0 0" where it leaves the product to the element-wise
-// one.  Host code only: nothing is launched.
+// One line of output each, host code only: nothing is launched.
+//   tile piece      of the any-size kernel through registers, "0 0" where it leaves the product to the element-wise one
+//   rows columns    tile of the ring kernel, "0 0" where that does not take the product in its place
+//   wide stream     whether output runs of 16 bytes are stored whole, and whether the ring kernel streams them
+//   tuned           tile side of the tile-aligned kernel, which comes before all of these, or 0
 #include <stdio.h>
 #include <string.h>
 
@@ -54,7 +57,10 @@ int main()
         }
         edge::Plan plan;
         const bool taken = edge::make_plan(g, &plan) == CUBE3D_OK;
-        printf("%d %d\n", taken ? plan.tile : 0, taken ? plan.piece : 0);
+        edge::RingPlan ring{0, 0, 0.f};
+        if (taken) ring = edge::ring_plan(g, plan);
+        printf("%d %d %d %d %d %d %d\n", taken ? plan.tile : 0, taken ? plan.piece : 0, ring.tile_m, ring.tile_n,
+               taken && plan.params.out_wide, ring.tile_m > 0 && edge::ring_streams(g, plan.params, ring), gemm_fast_tile(g));
     }
     return 0;
 }

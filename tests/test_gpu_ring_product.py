@@ -1,39 +1,33 @@
 """The ring kernel of the any-size product: every tile, operand layout and element type at contractions of one K-tile, of
 fewer K-tiles than the ring has stages, just above and below whole K-tiles and beyond the 64 that are looked up at a
-time; several tiles per workgroup; shards that end inside a K-tile.  Integers in [-4, 4]: all sums are exact (below
-2^24), so results are compared bit for bit with torch's fp32 product."""
-import os
-import subprocess
-
+time; several tiles per workgroup; results with streaming stores and element by element; shards that end inside a K-tile;
+operands at the limit of its addresses.  (That the sizes reach all this is asserted in test_product_dispatch.py.)
+Integers in [-4, 4]: all sums are exact (below 2^24), so results are compared bit for bit with torch's fp32 product."""
 import pytest
 import torch
 
 import paper_2105_14450_amd as c3
-from paper_2105_14450_amd import build
 
 import gpu_util as gu
+import product_shapes as ps
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CODES = {"f32": (torch.float32, c3.F32), "bf16": (torch.bfloat16, c3.BF16), "fp8_e4m3": (torch.float8_e4m3fn, c3.FP8_E4M3)}
 LAYOUT = {c3.FORM_AB: (1, 0), c3.FORM_ABT: (1, 1), c3.FORM_ATB: (0, 0)}
-# rows, columns, blocks per side of the cube, and contractions; multiples of 16 wherever an operand may be contiguous there
-SIZES = [(48, 1040, 1, (272, 1040, 2064)), (816, 1040, 1, (400, 1040)), (400, 1040, 1, (144, 1040, 8208)), (1616, 2064, 1, (272, 400, 1040)),
-         (2064, 4112, 1, (2064,)), (4112, 2064, 1, (1040, 2064)), (4112, 4112, 1, (80, 1040)), (272, 144, 3, (1040,)),
-         (3088, 1168, 1, (1040, 4624)), (1136, 7152, 1, (1040, 4112)), (2064, 3088, 1, (4112,))]
 CASES = [(dtype, out, form) for dtype, out in (("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16"), ("fp8_e4m3", "f32"))
          for form in LAYOUT]
+
+pytestmark = pytest.mark.gpu
 
 
 def _integers(shape, gen):
     return torch.randint(-4, 5, shape, device="cuda", generator=gen, dtype=torch.int8).float()
 
 
-@pytest.mark.gpu
 @pytest.mark.parametrize("dtype,out,form", CASES)
 def test_ring_tiles(dtype, out, form):
     storage, code = CODES[dtype]
     gen = torch.Generator(device="cuda").manual_seed(form)
-    for m, n, q, contractions in SIZES:
+    for m, n, q, contractions in ps.RING + ps.RING_LINES + (ps.RING_ODD if form == c3.FORM_ABT else []):
         for k in contractions:
             a, b = _integers((q ** 3, m, k), gen), _integers((q ** 3, k, n), gen)
             left = (a.transpose(1, 2) if form == c3.FORM_ATB else a).contiguous().to(storage)
@@ -48,9 +42,8 @@ def test_ring_tiles(dtype, out, form):
 # bits do not depend on that: a call with bf16 results is one with fp32 results rounded once, and the rows of a call with
 # few rows are those of one with many.  Random bytes, whose sums depend on the order in nearly every element; against 64 bits
 # one rounding to bf16 and 1e-4 of the largest entry for the matrix cores' sums.
-@pytest.mark.gpu
 @pytest.mark.parametrize("form", LAYOUT)
-@pytest.mark.parametrize("m,n,k", [(1616, 2064, 1040), (1136, 7152, 4112), (4112, 2064, 2064)])
+@pytest.mark.parametrize("m,n,k", ps.RING_DEEP)
 def test_fp8_bits_do_not_depend_on_the_tile(m, n, k, form):
     gen = torch.Generator(device="cuda").manual_seed(m + form)
 
@@ -78,7 +71,6 @@ def test_fp8_bits_do_not_depend_on_the_tile(m, n, k, form):
 
 # Tile-aligned fp8 products run on the tuned kernel with many rows and on the ring with few: the same bits too (no split of
 # the contraction at these sizes).  Random bytes; plain operands and a cube of one processor read in place.
-@pytest.mark.gpu
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 @pytest.mark.parametrize("form", LAYOUT)
 def test_fp8_bits_of_few_and_many_aligned_rows(form, out):
@@ -103,12 +95,11 @@ def test_fp8_bits_of_few_and_many_aligned_rows(form, out):
     assert torch.equal(plain[m][:256], plain[256])
 
 
-# q = 3: blocks of 3 shards that end inside a K-tile (of 64 to 256 indices), in every direction; a bias with the forward
-@pytest.mark.gpu
-@pytest.mark.parametrize("M,K,N", [(9 * 272, 3 * 656, 9 * 368), (9 * 304, 3 * 272, 9 * 272), (9 * 16, 3 * 1040, 9 * 272)])
+# shards that end inside a K-tile, of whole cache lines, of an odd number of columns; a bias with the forward
+@pytest.mark.parametrize("q,M,K,N", ps.RING_CUBES + ps.RING_CUBES_LINES + ps.RING_CUBES_ODD)
 @pytest.mark.parametrize("dtype", sorted(CODES))
-def test_ring_in_place(dtype, M, K, N):
-    q, (storage, code) = 3, CODES[dtype]
+def test_ring_in_place(dtype, q, M, K, N):
+    storage, code = CODES[dtype]
     result = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator(device="cuda").manual_seed(M)
     X, W, G, bias = _integers((M, K), gen), _integers((K, N), gen), _integers((M, N), gen), _integers((N,), gen)
@@ -124,18 +115,19 @@ def test_ring_in_place(dtype, M, K, N):
         assert torch.equal(got, gu.device_shards(want, name, q).to(result)), name
 
 
-@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="ROCm compiler not found")
-def test_sizes_reach_every_tile(tmp_path):
-    c3.binding.load()
-    exe = str(tmp_path / "ring_plan")
-    subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-I", build.INCLUDE, "-I", build.CSRC,
-                    os.path.join(ROOT, "tests", "host", "ring_plan.cpp"), "-x", "none", build.LIB,
-                    "-Wl,-rpath," + os.path.dirname(build.LIB), "-Wl,-rpath,/opt/rocm/lib", "-o", exe],
-                   check=True, capture_output=True)
-    asked = [(case, (m, n, q, k)) for case in CASES for m, n, q, ks in SIZES for k in ks]
-    lines = ["%d %d %d %d %d %d %d %d" % (CODES[t][1], CODES[o][1], *LAYOUT[f], q ** 3, m, n, k) for (t, o, f), (m, n, q, k) in asked]
-    res = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True, timeout=60)
-    reached = {(case, tuple(map(int, line.split()))) for (case, _), line in zip(asked, res.stdout.splitlines())}
-    tiles = lambda dtype: ((64, 64), (128, 128)) if dtype == "f32" else ((32, 32), (64, 64), (128, 128), (128, 256), (256, 128))
-    missing = {(case, tile) for case in CASES for tile in tiles(case[0])} - reached
-    assert not missing, sorted(missing)
+# An operand of 1 GiB at most is addressed through a buffer of that size, whose end marks rows and indices beyond the edges.
+@pytest.mark.parametrize("above", [False, True])
+@pytest.mark.parametrize("dtype", sorted(ps.ONE_GB))
+def test_operands_around_1_gb(dtype, above):
+    storage, code = CODES[dtype]
+    cols, n, rows = ps.ONE_GB[dtype][0], 16, ps.ONE_GB[dtype][2 if above else 1]
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    large, wide, tall = _integers((rows, cols), gen), _integers((cols, n), gen), _integers((rows, n), gen)
+    stored = large.to(storage)
+    for form, right, shape, want in ((c3.FORM_AB, wide, (rows, n, cols), large @ wide),
+                                     (c3.FORM_ABT, wide.t().contiguous(), (rows, n, cols), large @ wide),
+                                     (c3.FORM_ATB, tall, (cols, n, rows), large.t() @ tall)):
+        mm = c3.make_matmul(1, form, *shape, in_dtype=code, out_dtype=c3.F32)
+        got = torch.full(shape[:2], float("nan"), device="cuda")
+        c3.cube3d_matmul_blocks(mm, stored, right.to(storage), got)
+        assert torch.equal(got, want), "form %d" % form

@@ -1,5 +1,6 @@
 """Which kernel, tile and load width a product of any size runs on: the dispatch is host code, so it is asked on the
 CPU (``tests/host/product_plan.cpp`` linked against the library; nothing is launched)."""
+import collections
 import os
 import subprocess
 
@@ -16,8 +17,12 @@ LAYOUT = {c3.FORM_AB: (1, 0), c3.FORM_ABT: (1, 1), c3.FORM_ATB: (0, 0)}
 pytestmark = pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="ROCm compiler not found")
 
 
+Route = collections.namedtuple("Route", "tile piece rows columns wide stream tuned")
+
+
 @pytest.fixture(scope="session")
-def plans(tmp_path_factory):
+def routes(tmp_path_factory):
+    """What product_plan.cpp prints, one Route per line asked."""
     c3.binding.load()
     exe = str(tmp_path_factory.mktemp("plan") / "product_plan")
     subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-I", build.INCLUDE, "-I", build.CSRC,
@@ -27,8 +32,14 @@ def plans(tmp_path_factory):
 
     def ask(lines):
         res = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True, timeout=60)
-        return [tuple(map(int, line.split())) for line in res.stdout.splitlines()]
+        return [Route(*map(int, line.split())) for line in res.stdout.splitlines()]
     return ask
+
+
+@pytest.fixture(scope="session")
+def plans(routes):
+    """Tile side and load width of the any-size kernel (which the ring kernel takes in its place is not asked)."""
+    return lambda lines: [tuple(r[:2]) for r in routes(lines)]
 
 
 def plain(dtype, form, m, n, k, batch=1, out=c3.BF16):
@@ -85,6 +96,10 @@ def _kernel(dtype, tile, piece):
     return tile, 16 if piece >= 16 else 4 if piece >= 4 else {c3.F32: 4, c3.BF16: 2, c3.FP8_E4M3: 1}[dtype]
 
 
+NAMES = {"f32": c3.F32, "bf16": c3.BF16, "fp8_e4m3": c3.FP8_E4M3}
+OPS = (c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB)        # operand layouts of forward, dX and dW
+
+
 # The sizes of the GPU tests reach all 69 kernels, those of a cube in place every one with tiles of 64 and 128.
 def test_gpu_tests_reach_every_kernel(plans):
     widths = {c3.BF16: (16, 4, 2), c3.FP8_E4M3: (16, 4, 1), c3.F32: (16, 4)}
@@ -99,6 +114,60 @@ def test_gpu_tests_reach_every_kernel(plans):
     layouts = tuple(LAYOUT[f] for f in (c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB))
     reached = {(t, layouts[op], *_kernel(t, *plan)) for (t, op, _), plan in zip(asked, plans([a[2] for a in asked])) if plan[0]}
     assert reached >= {x for x in every if x[2] > 32}, {x for x in every if x[2] > 32} - reached
+
+
+RING_TYPES = [(t, out) for t, out in (("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16"), ("fp8_e4m3", "f32"))]
+
+
+def _ring_tiles(dtype):
+    return ((64, 64), (128, 128)) if dtype == "f32" else ((32, 32), (64, 64), (128, 128), (128, 256), (256, 128))
+
+
+# The sizes of test_gpu_ring_product.py reach every tile in every type and layout, on both sides of what the kernel decides by
+# the result: streaming stores (tiles above 128 x 128), elements one by one (A B^T on plain operands).
+def test_gpu_tests_reach_every_ring_kernel(routes):
+    asked = [((t, out, form), plain(NAMES[t], form, m, n, k, q ** 3, NAMES[out])) for t, out in RING_TYPES for form in LAYOUT
+             for m, n, q, ks in ps.RING + ps.RING_LINES + (ps.RING_ODD if form == c3.FORM_ABT else []) for k in ks]
+    reached = {(*case, (r.rows, r.columns), r.wide, r.stream)
+               for (case, _), r in zip(asked, routes([line for _, line in asked])) if r.rows and not r.tuned}
+    want = set()
+    for t, out in RING_TYPES:
+        for tile in _ring_tiles(t):
+            large = tile[0] * tile[1] > 128 * 128
+            want |= {(t, out, form, tile, 1, s) for form in LAYOUT for s in ((0, 1) if large else (0,))}
+            want.add((t, out, c3.FORM_ABT, tile, 0, 0))
+    assert not want - reached, sorted(want - reached)
+
+
+# The sizes at which the bits of fp8 products are compared between tiles.
+def test_compared_fp8_products_run_on_different_tiles(routes):
+    tiles = lambda rows: {(f, (r.rows, r.columns)) for f in LAYOUT for r in
+                          routes([plain(c3.FP8_E4M3, f, rows or m, n, k) for m, n, k in ps.RING_DEEP]) if not r.tuned}
+    assert tiles(0) == {(f, t) for f in LAYOUT for t in ((128, 128), (128, 256), (256, 128))}
+    assert {t for rows in (400, 48) for _, t in tiles(rows)} >= {(32, 32), (64, 64)}
+
+
+# In place: streaming stores in every layout, elements one by one in dX (an odd number of rows of W) and dW (of columns).
+def test_gpu_tests_reach_every_way_of_storing_in_place(routes):
+    for name in ("bf16", "fp8_e4m3", "f32"):
+        asked = [(op, cube(NAMES[name], op, *sizes, out=c3.F32 if name == "f32" else c3.BF16))
+                 for sizes in ps.RING_CUBES + ps.RING_CUBES_LINES + ps.RING_CUBES_ODD for op in range(3)]
+        reached = {(op, r.wide, r.stream) for (op, _), r in zip(asked, routes([line for _, line in asked])) if r.rows and not r.tuned}
+        want = {(op, 1, 0) for op in range(3)} | {(1, 0, 0)}
+        if name == "bf16":
+            want |= {(2, 0, 0)} | {(op, 1, 1) for op in range(3)}
+        if name == "fp8_e4m3":
+            want |= {(0, 1, 1), (2, 1, 1)}
+        assert not want - reached, (name, want - reached)
+
+
+@pytest.mark.parametrize("name", sorted(ps.ONE_GB))
+def test_operands_above_1_gb_are_kept_off_the_ring(routes, name):
+    cols, most, above = ps.ONE_GB[name]
+    forms = (c3.FORM_AB, c3.FORM_ABT) + ((c3.FORM_ATB,) if name != "f32" else ())      # (fp32 with few rows has its own kernel)
+    for rows, taken in ((most, True), (above, False)):
+        lines = [plain(NAMES[name], form, *((cols, 16, rows) if form == c3.FORM_ATB else (rows, 16, cols)), out=c3.F32) for form in forms]
+        assert [r.rows > 0 for r in routes(lines)] == [taken] * len(forms)
 
 
 @pytest.mark.parametrize("name,dtype", [("f32", c3.F32), ("bf16", c3.BF16), ("fp8_e4m3", c3.FP8_E4M3)])
