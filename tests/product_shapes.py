@@ -14,6 +14,12 @@ CUBES = {16: ((9 * 216, 3 * 656, 9 * 224), (9 * 64, 3 * 336, 9 * 144)),
          4: ((9 * 220, 3 * 660, 9 * 228), (9 * 60, 3 * 332, 9 * 140)),
          1: ((9 * 217, 3 * 661, 9 * 227), (9 * 59, 3 * 331, 9 * 139))}
 
+# in place, q = 8: shards of the contraction index that are shorter than a K-tile (32 fp32, 64 bf16 or 128 fp8 indices) keep
+# a product off the ring kernel: the 16-byte kernels through registers
+SHORT_SHARDS = {"bf16": ((3584, 2112, 3584), (2112, 448, 2048), (192, 448, 3584), (64, 448, 3584), (576, 448, 1024)),
+                "fp8_e4m3": ((7168, 896, 4096), (2112, 896, 4096), (576, 896, 2048), (64, 896, 7168), (576, 128, 1024)),
+                "f32": ((1792, 2112, 1792), (1792, 1056, 1792), (1792, 160, 1792), (1088, 224, 1792), (64, 224, 1792))}
+
 # ring kernel: (rows, columns, blocks per side of the cube, contractions).  Multiples of 16 wherever an operand may be
 # contiguous there; output rows that are not whole cache lines
 RING = [(48, 1040, 1, (272, 1040, 2064)), (816, 1040, 1, (400, 1040)), (400, 1040, 1, (144, 1040, 8208)), (1616, 2064, 1, (272, 400, 1040)),

@@ -99,7 +99,8 @@ def test_very_many_thin_blocks():
     assert torch.equal(c, b.mul_(a))            # products of integers up to 4: exact
 
 
-# ---- every kernel of the any-size product (which sizes reach which is asserted in test_product_dispatch.py) ----
+# ---- every kernel of the any-size product (which sizes reach which is asserted in test_product_dispatch.py; of the 16-byte
+# ones most only with shards shorter than a K-tile, the ring kernel takes their other sizes) ----
 # Integers in [-4, 4] on the device; the reference is torch's fp32 product (exact: sums stay below 2^24), rounded once.
 
 CODES = {"f32": (torch.float32, c3.F32), "bf16": (torch.bfloat16, c3.BF16), "fp8_e4m3": (torch.float8_e4m3fn, c3.FP8_E4M3)}
@@ -134,24 +135,34 @@ def test_every_tile_and_load_width(dtype, out, unit, form):
             _exactly(got, a @ b, "%d x %d x %d" % (m, n, k))
 
 
+def _in_place(dtype, q, M, K, N, gen):
+    """The three products of a layer on its shards, a bias with the forward, against torch."""
+    storage, code = CODES[dtype]
+    result = torch.float32 if dtype == "f32" else torch.bfloat16
+    X, W, G, bias = _integers((M, K), gen), _integers((K, N), gen), _integers((M, N), gen), _integers((N,), gen)
+    d = c3.make_desc(q, M, K, N, in_dtype=code, out_dtype=c3.F32, shard_dtype=CODES["f32" if dtype == "f32" else "bf16"][1])
+    x, w, g = (gu.device_shards(t, name, q).to(storage) for t, name in ((X, "x"), (W, "w"), (G, "y")))
+    diagonal = torch.zeros((q ** 3, N // q ** 2), device="cuda")
+    c3.virtual_cube_scatter(d, c3.OPERAND_BIAS, bias, diagonal)
+    y, dx, dw = _nan(g.shape, result), _nan(x.shape, result), _nan(w.shape, result)
+    c3.virtual_cube_linear_fwd(d, x, w, diagonal, y)
+    c3.virtual_cube_linear_bwd_dx(d, g, w, dx)
+    c3.virtual_cube_linear_bwd_dw(d, x, g, dw)
+    for got, want, name in ((y, X @ W + bias, "y"), (dx, G @ W.t(), "x"), (dw, X.t() @ G, "w")):
+        _exactly(got, gu.device_shards(want, name, q), "%s of %d x %d x %d" % (name, M, K, N))
+
+
 @pytest.mark.parametrize("unit", sorted(ps.CUBES))
 @pytest.mark.parametrize("dtype", ["bf16", "f32", "fp8_e4m3"])
 def test_every_tile_in_place_with_bias(dtype, unit):
-    q, (storage, code) = 3, CODES[dtype]
-    result = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator(device="cuda").manual_seed(100 + unit)
     for M, K, N in ps.CUBES[unit]:
-        X, W, G, bias = _integers((M, K), gen), _integers((K, N), gen), _integers((M, N), gen), _integers((N,), gen)
-        d = c3.make_desc(q, M, K, N, in_dtype=code, out_dtype=c3.F32, shard_dtype=CODES["f32" if dtype == "f32" else "bf16"][1])
-        x, w, g = (gu.device_shards(t, name, q).to(storage) for t, name in ((X, "x"), (W, "w"), (G, "y")))
-        diagonal = torch.zeros((q ** 3, N // q ** 2), device="cuda")
-        c3.virtual_cube_scatter(d, c3.OPERAND_BIAS, bias, diagonal)
-        y, dx, dw = _nan(g.shape, result), _nan(x.shape, result), _nan(w.shape, result)
-        c3.virtual_cube_linear_fwd(d, x, w, diagonal, y)
-        c3.virtual_cube_linear_bwd_dx(d, g, w, dx)
-        c3.virtual_cube_linear_bwd_dw(d, x, g, dw)
-        for got, want, name in ((y, X @ W + bias, "y"), (dx, G @ W.t(), "x"), (dw, X.t() @ G, "w")):
-            _exactly(got, gu.device_shards(want, name, q), "%s of %d x %d x %d" % (name, M, K, N))
+        _in_place(dtype, 3, M, K, N, gen)
+
+
+@pytest.mark.parametrize("dtype,M,K,N", [(dtype, *sizes) for dtype in sorted(ps.SHORT_SHARDS) for sizes in ps.SHORT_SHARDS[dtype]])
+def test_shards_shorter_than_a_k_tile(dtype, M, K, N):
+    _in_place(dtype, 8, M, K, N, torch.Generator(device="cuda").manual_seed(M))
 
 
 # An operand just below 4 GB is addressed by 32-bit offsets that nearly wrap; above, the element-wise kernel takes it.

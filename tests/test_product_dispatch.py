@@ -100,20 +100,25 @@ NAMES = {"f32": c3.F32, "bf16": c3.BF16, "fp8_e4m3": c3.FP8_E4M3}
 OPS = (c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB)        # operand layouts of forward, dX and dW
 
 
-# The sizes of the GPU tests reach all 69 kernels, those of a cube in place every one with tiles of 64 and 128.
-def test_gpu_tests_reach_every_kernel(plans):
+# The sizes of the GPU tests reach all 69 kernels through registers, those of a cube in place every one with tiles of 64 and
+# 128.  What the ring kernel or the tile-aligned one takes does not count.
+def test_gpu_tests_reach_every_kernel(routes):
     widths = {c3.BF16: (16, 4, 2), c3.FP8_E4M3: (16, 4, 1), c3.F32: (16, 4)}
     every = {(t, layout, tile, w) for t in widths for layout in LAYOUT.values() for tile in (32, 64, 128) for w in widths[t]
              if not (w == 1 and tile == 128)}
     assert len(every) == 69
-    asked = [(t, form, plain(t, form, m, n, k)) for t in widths for form in LAYOUT for u in ps.OUTPUTS
-             for m, n in ps.OUTPUTS[u] for k in ps.CONTRACTIONS[u]]
-    reached = {(t, LAYOUT[form], *_kernel(t, *plan)) for (t, form, _), plan in zip(asked, plans([a[2] for a in asked])) if plan[0]}
-    assert reached == every
-    asked = [(t, op, cube(t, op, 3, *sizes)) for t in widths for op in range(3) for u in ps.CUBES for sizes in ps.CUBES[u]]
-    layouts = tuple(LAYOUT[f] for f in (c3.FORM_AB, c3.FORM_ABT, c3.FORM_ATB))
-    reached = {(t, layouts[op], *_kernel(t, *plan)) for (t, op, _), plan in zip(asked, plans([a[2] for a in asked])) if plan[0]}
-    assert reached >= {x for x in every if x[2] > 32}, {x for x in every if x[2] > 32} - reached
+
+    def run(asked):
+        return {(t, LAYOUT[form], *_kernel(t, r.tile, r.piece)) for (t, form, _), r in zip(asked, routes([a[2] for a in asked]))
+                if r.tile and not r.rows and not r.tuned}
+    result = lambda t: c3.F32 if t == c3.F32 else c3.BF16
+    plain_asked = [(t, form, plain(t, form, m, n, k, out=result(t))) for t in widths for form in LAYOUT for u in ps.OUTPUTS
+                   for m, n in ps.OUTPUTS[u] for k in ps.CONTRACTIONS[u]]
+    cubes = [(t, 3, sizes) for t in widths for u in ps.CUBES for sizes in ps.CUBES[u]]
+    cubes += [(NAMES[name], 8, sizes) for name in ps.SHORT_SHARDS for sizes in ps.SHORT_SHARDS[name]]
+    in_place = run([(t, OPS[op], cube(t, op, q, *sizes, out=result(t))) for t, q, sizes in cubes for op in range(3)])
+    assert run(plain_asked) | in_place == every, every - run(plain_asked) - in_place
+    assert in_place >= {x for x in every if x[2] > 32}, {x for x in every if x[2] > 32} - in_place
 
 
 RING_TYPES = [(t, out) for t, out in (("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32"), ("fp8_e4m3", "bf16"), ("fp8_e4m3", "f32"))]
