@@ -217,6 +217,20 @@ int64_t longest_ring_ktile(const AxisMap &mn, const AxisMap &k, bool kmajor, int
     return longest;
 }
 
+// Results that are stored element by element (output rows that are not whole 16-byte pieces) cost a tile of the ring kernel more
+// than one of the kernel through registers: bytes of contraction from which the ring makes up for that.  Ring against
+// registers, A B^T of an odd number of columns: tiles of 256 x 128 took 1.5 times as long at 512 bytes (bf16), 1.2 at 4096 and 0.9 at
+// 16384; tiles of 64 with fp32 results 1.03 at 512, 0.98 at 1024.  Of 14149 products 3986 took over 4 % longer on the ring, with
+// these lines 227.  (fp32 operands: no tiles of 128 for such results, 1.08-1.23 at every length; 0.87 in tiles of 64.)
+int64_t least_narrow_bytes(const RingPlan &r, bool f32, bool fp8, bool wide_results)
+{
+    const int area = r.tile_m * r.tile_n;
+    if (area <= 32 * 32) return 768;
+    if (area <= 64 * 64) return wide_results && !f32 ? 1024 : 256;
+    if (fp8 && !wide_results) return 4096;
+    return area == 128 * 128 && !fp8 ? 12288 : 8192;
+}
+
 }  // namespace
 
 namespace edge {
@@ -242,6 +256,7 @@ RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
         const RingCost &c = costs[i];
         const int kb = ring_ktile_bytes(c.tile_n);
         if (kb / es > longest_a || kb / es > longest_b) continue;
+        if (f32 && !plan.params.out_wide && c.tile_m > 64) continue;      // (least_narrow_bytes)
         const int64_t items = ((g.Mo + c.tile_m - 1) / c.tile_m) * ((g.No + c.tile_n - 1) / c.tile_n) * g.batch;
         const bool pair = c.pair > 0.f && items > cus;
         const float rounds = (float)((items + (pair ? 2 : 1) * cus - 1) / ((pair ? 2 : 1) * cus)), ktiles = (float)((g.Kc * es + kb - 1) / kb);
@@ -250,6 +265,7 @@ RingPlan ring_plan(const GemmArgs &g, const Plan &plan)
         const float us = c.start + rounds * (item + ktiles * ktime);
         if (best.tile_m == 0 || us < best.us) best = RingPlan{c.tile_m, c.tile_n, us};
     }
+    if (best.tile_m > 0 && !plan.params.out_wide && g.Kc * es < least_narrow_bytes(best, f32, fp8, wide)) return RingPlan{0, 0, 0.f};
     return best;
 }
 

@@ -30,12 +30,13 @@ RING_DEEP = [(1616, 2064, 1040), (1136, 7152, 4112), (1552, 8256, 400)]
 # more than 16 MB of results in rows of whole cache lines: streaming stores
 RING_LINES = [(1552, 8256, 1, (144, 400)), (2064, 7232, 1, (144,)), (592, 1088, 3, (144,))]
 # A B^T of an odd number of columns: results are stored element by element
-RING_ODD = [(3001, 145, 1, (272,)), (2049, 1041, 1, (272,)), (45, 33, 1, (272,)), (4001, 1041, 1, (272,)), (1105, 7151, 1, (272,))]
+RING_ODD = [(45, 33, 1, (784,)), (3001, 145, 1, (784,)), (4001, 145, 1, (784,)), (1105, 1041, 1, (6160,)), (4001, 1041, 1, (8208,)),
+            (2049, 1041, 1, (8208,)), (3001, 4111, 1, (4112,)), (1105, 7151, 1, (8208,))]
 # in place (q, M, K, N): shards that end inside a K-tile, in every direction
 RING_CUBES = [(3, 9 * 272, 3 * 656, 9 * 368), (3, 9 * 304, 3 * 272, 9 * 272), (3, 9 * 16, 3 * 1040, 9 * 272)]
 # whole cache lines and more than 16 MB; shards of an odd number of columns or rows
 RING_CUBES_LINES = [(3, 9 * 272, 3 * 1344, 9 * 576), (3, 9 * 464, 3 * 1344, 9 * 64)]
-RING_CUBES_ODD = [(2, 4 * 528, 2 * 1041, 4 * 528), (2, 4 * 272, 2 * 337, 4 * 336), (2, 4 * 136, 2 * 200, 4 * 68), (2, 4 * 544, 2 * 2048, 4 * 516)]
+RING_CUBES_ODD = [(2, 4 * 528, 2 * 1041, 4 * 2064), (2, 4 * 272, 2 * 337, 4 * 336), (2, 4 * 136, 2 * 200, 4 * 68), (2, 4 * 1552, 2 * 2048, 4 * 516)]
 # an operand [rows, columns] at most and just above 1 GiB, the ring kernel's limit: (columns, rows at most, rows above)
 ONE_GB = {"f32": (1040, 258096, 258112), "bf16": (1040, 516208, 516224), "fp8_e4m3": (1040, 1032432, 1032448)}
 

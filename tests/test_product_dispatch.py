@@ -140,8 +140,21 @@ def test_gpu_tests_reach_every_ring_kernel(routes):
         for tile in _ring_tiles(t):
             large = tile[0] * tile[1] > 128 * 128
             want |= {(t, out, form, tile, 1, s) for form in LAYOUT for s in ((0, 1) if large else (0,))}
-            want.add((t, out, c3.FORM_ABT, tile, 0, 0))
+            if t != "f32" or tile == (64, 64):
+                want.add((t, out, c3.FORM_ABT, tile, 0, 0))
     assert not want - reached, sorted(want - reached)
+
+
+# Results stored element by element: the ring takes 1.1 to 2.6 times as long as the kernel through registers on the first of each
+# pair, and less on the second, which has a longer contraction.
+@pytest.mark.parametrize("dtype,out,batch,m,n,k,longer", [
+    (c3.BF16, c3.BF16, 1, 1067, 5893, 40, 8192), (c3.BF16, c3.F32, 1, 4001, 1041, 784, 8208), (c3.FP8_E4M3, c3.BF16, 8, 4175, 35, 384, 4096),
+    (c3.FP8_E4M3, c3.F32, 64, 65, 2057, 80, 8192), (c3.BF16, c3.F32, 1, 1000, 333, 256, 1024)])
+def test_odd_results_of_short_contractions_stay_off_the_ring(routes, dtype, out, batch, m, n, k, longer):
+    short, long = routes([plain(dtype, c3.FORM_ABT, m, n, x, batch, out) for x in (k, longer)])
+    assert not short.rows and long.rows and not short.wide and not long.wide
+    for f32_out in (c3.F32, c3.BF16):       # fp32 operands: tiles of 64
+        assert [(r.rows, r.columns) for r in routes([plain(c3.F32, c3.FORM_ABT, 3001, 2001, x, out=f32_out) for x in (512, 4096)])] == [(64, 64)] * 2
 
 
 # The sizes at which the bits of fp8 products are compared between tiles.
