@@ -101,13 +101,16 @@ int build_gemm(const cube3d_desc *d, int op, int batch, const void *A, const voi
 
 size_t workspace_for(const GemmArgs &a)
 {
-    return gemm_fast_workspace(a);
+    return gemm_fast_workspace(a, gemm_fast_plan(a));
 }
 
 // The first kernel family that takes the product: tile-aligned sizes, then any size, then element by element.
 int run_gemm(const GemmArgs &a)
 {
-    int rc = gemm_fast(a);
+    const FastPlan plan = gemm_fast_plan(a);
+    const size_t need = gemm_fast_workspace(a, plan);
+    if (need > 0 && (!a.workspace || a.workspace_bytes < need)) return CUBE3D_EWORKSPACE;
+    int rc = gemm_fast(a, plan);
     if (rc == CUBE3D_ENOTIMPL) rc = gemm_edge(a);
     return rc == CUBE3D_ENOTIMPL ? gemm_generic(a) : rc;
 }
@@ -124,8 +127,6 @@ int run_product(const cube3d_desc *d, int op, int i, int j, int l, const void *A
     GemmArgs a;
     rc = build_gemm(d, op, batch, A, B, C, ws, ws_bytes, stream, &a);
     if (rc != CUBE3D_OK) return rc;
-    const size_t need = workspace_for(a);
-    if (need > 0 && (!ws || ws_bytes < need)) return CUBE3D_EWORKSPACE;
     return run_gemm(a);
 }
 
@@ -573,8 +574,6 @@ int cube3d_matmul_blocks(const cube3d_matmul *mm, const void *A_blocks, const vo
     a.workspace = workspace;
     a.workspace_bytes = workspace_bytes;
     a.stream = static_cast<hipStream_t>(stream);
-    const size_t need = workspace_for(a);
-    if (need > 0 && (!workspace || workspace_bytes < need)) return CUBE3D_EWORKSPACE;
     return run_gemm(a);
 }
 

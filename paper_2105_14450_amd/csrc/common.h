@@ -50,8 +50,7 @@ struct AxisMap {
 inline void prepare_axis_map(AxisMap &m)
 {
     auto magic = [](int32_t P, uint64_t *M, int32_t *N) {
-        int L = 0;
-        while ((1ll << L) < P) ++L;
+        const int L = P > 1 ? 32 - __builtin_clz((unsigned)(P - 1)) : 0;      // ceil(log2 P)
         *N = 31 + L;
         *M = ((1ull << *N) + (unsigned)P - 1) / (unsigned)P;      // N <= 62
     };
@@ -123,11 +122,14 @@ int gemm_edge(const GemmArgs &g);
 // Estimated time in us where its ring kernel takes the product, else infinity.
 float gemm_edge_estimate(const GemmArgs &g);
 
-// Tuned bf16 / fp8 path; returns CUBE3D_ENOTIMPL when the shape does not fit its tiles.
-int gemm_fast(const GemmArgs &g);
-// Tile side it takes the product with, 0 if it does not.
-int gemm_fast_tile(const GemmArgs &g);
-size_t gemm_fast_workspace(const GemmArgs &g);
+// Tuned bf16 / fp8 path.  What it runs a product on: a pure function of the shape, made once per call.
+struct FastPlan {
+    int tile;     // 256 or 128 (square output tile); 0 = not supported by the tuned kernel, or not the fastest
+    int splits;
+};
+FastPlan gemm_fast_plan(const GemmArgs &g);
+size_t gemm_fast_workspace(const GemmArgs &g, const FastPlan &plan);
+int gemm_fast(const GemmArgs &g, const FastPlan &plan);      // CUBE3D_ENOTIMPL where plan.tile is 0
 // Launch of the tuned kernel's map-addressed instantiations (tile = 256 or 128, chosen by gemm_fast).
 int gemm_fast_mapped(const GemmArgs &g, int tile);
 

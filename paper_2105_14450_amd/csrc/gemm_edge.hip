@@ -13,7 +13,7 @@ constexpr int64_t MAX_EXTENT = (1ll << 31) - 4096;   // indices stay below 2^31,
 // widest power of two up to 16 / es elements that divides `x`
 int64_t common_piece(int64_t piece, int64_t x)
 {
-    while (x % piece) piece /= 2;
+    while (x & (piece - 1)) piece /= 2;
     return piece;
 }
 

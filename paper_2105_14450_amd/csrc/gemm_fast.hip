@@ -8,11 +8,6 @@ using namespace mfk;
 
 namespace {
 
-struct Plan {
-    int tile;     // 256 or 128 (square output tile); 0 = shape not supported by the tuned kernel
-    int splits;
-};
-
 // What the map-addressed instantiations assume of an index placement.
 //   walked (the contraction index): shards are whole passes over the LDS stages long (`granule` indices),
 //     so that a K-tile never straddles a shard and boundaries fall on pass boundaries
@@ -34,10 +29,12 @@ bool map_ok(const AxisMap &m, int64_t extent, int64_t stride_align, bool contigu
 constexpr double T_KTILE_256_US = 0.44, T_KTILE_128_US = 0.14, T_WORKGROUP_US = 4.0, T_REDUCE_LAUNCH_US = 3.0,
                  REDUCE_BYTES_PER_US = 2.5e6;
 
+}  // namespace
+
 // Pure function of the shape, so that cube3d_workspace_bytes() and the launch agree.
-Plan make_plan(const GemmArgs &g)
+FastPlan gemm_fast_plan(const GemmArgs &g)
 {
-    Plan p{0, 1};
+    FastPlan p{0, 1};
     const int NUM_CU = num_compute_units();
     const bool fp8 = g.in_dtype == CUBE3D_FP8_E4M3;
     if (g.in_dtype != CUBE3D_BF16 && !fp8) return p;
@@ -116,6 +113,8 @@ Plan make_plan(const GemmArgs &g)
     return p;
 }
 
+namespace {
+
 // out[b][m][n] = sum over s (ascending) of ws[b][s][m][n], rounded once to the output type.
 template <typename TOut>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ ws, TOut *__restrict__ out,
@@ -163,7 +162,7 @@ int launch_for_layout(const GemmArgs &g, int splits, void *out, int64_t ld, int6
     return launch_layout<E, T, T, 64, 4, TOut>(g, splits, out, ld, bs, ss, g.alpha);
 }
 
-template <typename E, int T, typename TOut> int run_tile(const GemmArgs &g, const Plan &pl)
+template <typename E, int T, typename TOut> int run_tile(const GemmArgs &g, const FastPlan &pl)
 {
     if (pl.splits == 1) return launch_for_layout<E, T, TOut>(g, 1, g.C, g.ldc, g.strideC, 0);
     // the scale is applied once, to the partials, before the fixed-order sum
@@ -179,18 +178,14 @@ template <typename E, int T, typename TOut> int run_tile(const GemmArgs &g, cons
 
 }  // namespace
 
-size_t gemm_fast_workspace(const GemmArgs &g)
+size_t gemm_fast_workspace(const GemmArgs &g, const FastPlan &pl)
 {
-    const Plan pl = make_plan(g);
     if (pl.tile == 0 || pl.splits == 1) return 0;
     return (size_t)g.batch * pl.splits * g.Mo * g.No * sizeof(float);
 }
 
-int gemm_fast_tile(const GemmArgs &g) { return make_plan(g).tile; }
-
-int gemm_fast(const GemmArgs &g)
+int gemm_fast(const GemmArgs &g, const FastPlan &pl)
 {
-    const Plan pl = make_plan(g);
     if (pl.tile == 0) return CUBE3D_ENOTIMPL;
     if (g.maps) return gemm_fast_mapped(g, pl.tile);
     const bool f32 = g.out_dtype == CUBE3D_F32;

@@ -60,7 +60,7 @@ int main()
         edge::RingPlan ring{0, 0, 0.f};
         if (taken) ring = edge::ring_plan(g, plan);
         printf("%d %d %d %d %d %d %d\n", taken ? plan.tile : 0, taken ? plan.piece : 0, ring.tile_m, ring.tile_n,
-               taken && plan.params.out_wide, ring.tile_m > 0 && edge::ring_streams(g, plan.params, ring), gemm_fast_tile(g));
+               taken && plan.params.out_wide, ring.tile_m > 0 && edge::ring_streams(g, plan.params, ring), gemm_fast_plan(g).tile);
     }
     return 0;
 }
