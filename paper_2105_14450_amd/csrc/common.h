@@ -119,8 +119,8 @@ int gemm_generic(const GemmArgs &g);
 // Any size and dtype; CUBE3D_ENOTIMPL where gemm_generic is faster (short contractions) or has to take it: operands that
 // span 4 GB or more, 2^24 tiles or more; also what gemm_generic refuses (more than 64 * 65535 rows, 65535 blocks).
 int gemm_edge(const GemmArgs &g);
-// Estimated time in us where its ring kernel takes the product, else infinity.
-float gemm_edge_estimate(const GemmArgs &g);
+// Whether its ring kernel takes a tile-aligned product and is safely below `us` microseconds by its estimate.
+bool gemm_edge_takes_less(const GemmArgs &g, double us);
 
 // Tuned bf16 / fp8 path.  What it runs a product on: a pure function of the shape, made once per call.
 struct FastPlan {
