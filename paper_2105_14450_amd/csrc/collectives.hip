@@ -406,8 +406,13 @@ int launch_reduce(const CubeGeom &g, int mode, int64_t rows, int64_t seg, const 
         else
             hipLaunchKernelGGL((cube_reduce_kernel<TIn, TOut, 1, false, RPW>), grid, dim3(256), 0, stream, g, mode, rows, p, s, bias);
     };
-    // Four rows one after the other cost a wavefront four memory latencies: with fewer than eight workgroups per CU it takes one.
-    if (n * ((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) < 2048) launch(std::integral_constant<int, 1>{});
+    // Four rows one after the other cost a wavefront four memory latencies; one row each cost four times the workgroups, which
+    // start no faster than about 1 per ns.  One row while there are at most four workgroups per CU and 64-lane step of the row (21240
+    // sizes, one row against four: 0.84-0.95 of the time at 512-1024 workgroups and one step, 1.2-1.3 at 2048-4096, 1.35-1.47
+    // beyond; rows of eight steps 0.92 at 4096-8192), and fewer than eight per CU with four rows each.
+    const int64_t cus = num_compute_units(), steps = (seg + (seg % 4 ? 63 : 255)) / (seg % 4 ? 64 : 256);
+    if (n * ((rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) < 8 * cus && n * ((rows + 3) / 4) <= 4 * cus * steps)
+        launch(std::integral_constant<int, 1>{});
     else launch(std::integral_constant<int, ROWS_PER_BLOCK / 4>{});
     return launch_status();
 }
