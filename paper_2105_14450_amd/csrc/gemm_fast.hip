@@ -108,7 +108,7 @@ FastPlan gemm_fast_plan(const GemmArgs &g)
     if ((int64_t)g.batch * splits > 65535) splits = 1;
     p.splits = splits;
     // Half of the CUs or more without a tile: the ring kernel's smaller ones take less time (bf16, us here / there: dX
-    // 2048 x 512 x 2048, 64 tiles, 14.2 / 9.9; dW 512 x 2048 x 2048 12.5 / 9.9; but 2048 x 2048 x 512, 256 tiles, 7.5 / 10.1)
+    // 2048 x 512 x 2048, 64 tiles, 13.8 / 9.9; dW 512 x 2048 x 2048 12.1 / 9.2; but 2048 x 2048 x 512, 256 tiles, 6.9 / 10.1)
     // Not asked where split-K won: over 8473 such products the ring would take 0.73 of the time in the mean (128 x 2048 x 2048 bf16,
     // both K-major, 11.1 us by the estimate here, 6.5 there), and over 4 % longer on 421, up to 1.55 times (fp8, both MN-major).
     if (splits == 1 && 2 * tiles <= NUM_CU && gemm_edge_takes_less(g, best)) p.tile = 0;

@@ -5,13 +5,16 @@
 // LDS, into a ring of NST stages of one K-tile each), four multiply, one of either on every SIMD.  A direct-to-LDS load holds
 // its wavefront up until the CU's 64 bytes per cycle have room for it, 64 cycles with four wavefronts loading: wavefronts
 // that also multiply leave the matrix cores idle meanwhile, and the load path while they multiply.  2032 x 512 x 2048
-// bf16, both operands K-major, tiles of 64: 12.4 us without loaders, 9.0 with, 13.8 in gemm_edge.h.  The loaders run on
-// into the next tile while the output of the last one is stored.
+// bf16, both operands K-major, tiles of 64: 12.4 us without loaders, 9.0-9.8 with, 13.8-15.0 in gemm_edge.h.  The loaders run
+// on into the next tile while the output of the last one is stored, as far as the ring's stages go: vmcnt counts stores too, so
+// the multipliers' first barrier behind an output waits until it has left.
 //
 // What bounds it (bf16, cycles per 128 bytes of contraction at 2.3 GHz).  Tiles of 64: the load path, 256 of 300.  Tiles of
 // 128: 512 for the loads and 512 for the MFMAs, 700.  256 x 128: MFMAs, 1024 of 1150-1250, and one or a few tiles per CU.
-// 8000 x 8192 x 2048: 225-240 us = 1.12-1.19 PFLOP/s, 318 in gemm_edge.h; three fp8 products of 3000 x 3072 x 12288 331 us =
-// 2.05 PFLOP/s against 585.  Few rows (64 x 8192 x 2048 14.6 -> 11, 64 x 2048 x 8192 24 -> 21): one workgroup's K loop.
+// 8000 x 8192 x 2048: 225-240 us = 1.12-1.19 PFLOP/s, 318-329 in gemm_edge.h; three fp8 products of 3000 x 3072 x 12288
+// 356-361 us = 1.9 PFLOP/s against 597.  Few rows (64 x 8192 x 2048 14.7 -> 11, 64 x 2048 x 8192 23 -> 22): one workgroup's K loop.
+// fp8 operands with 256-byte LDS rows (MN-major, tiles 256 wide) are read with two-way bank conflicts: Fp8::mn_swz deals
+// consecutive k-rows out for rows of 128 bytes.
 //
 // Edges.  The loads go through a buffer descriptor of 1 GiB: an offset beyond it reads as zeros, so rows beyond the
 // output, indices beyond the contraction and K-tiles beyond the last one are loads like any other, and the number of loads
